@@ -19,9 +19,9 @@
 // vertex stay in the FP64 near-field operator.
 //
 // Product y = B x: z_b = V_b^T x_sigma per admissible block, then per leaf
-// of the test tree (one workgroup, fixed order: the admissible blocks of its
-// ancestors from the root down, then its dense blocks) y_rows = sum U_b z_b +
-// sum D x, FP64 sums of FP32 entries; finally the near-field CSR.  The result
+// of the test tree (ranges of its columns, fixed order: the admissible blocks of
+// its ancestors from the root down, then its dense blocks) y_rows = sum U_b z_b
+// + sum D x, FP64 sums of FP32 entries; finally the near-field CSR.  The result
 // is deterministic.
 #include <algorithm>
 #include <chrono>
@@ -31,6 +31,7 @@
 
 #include "bem_internal.h"
 #include "entries.h"
+#include "near_row.h"
 
 namespace bem {
 
@@ -39,7 +40,7 @@ namespace {
 using namespace entries;
 
 constexpr int ACA_THREADS = 256;
-constexpr int ROW_THREADS = 128;   // product: one thread per row of a leaf (2 x leaf <= 128)
+constexpr int MAX_LEAF = 64;   // vertices per leaf cluster at most
 
 // ---------------------------------------------------------------- host tree
 struct Cluster {
@@ -519,6 +520,7 @@ __global__ __launch_bounds__(256) void hmat_z_kernel(const LrBlock *blocks, cons
     for (int l = wave; l < B.rank; l += 4) {
         const float2 *v = V + B.voff + (int64_t)l * n2;
         double sr = 0, si = 0;
+#pragma unroll 4
         for (int q = lane; q < n2; q += 64) {
             const int d = q >= B.n ? 1 : 0;
             const float2 a = v[q], b = xt[d * N + B.c0 + q - d * B.n];
@@ -533,69 +535,116 @@ __global__ __launch_bounds__(256) void hmat_z_kernel(const LrBlock *blocks, cons
     }
 }
 
-// Rows of one test leaf: y = sum over the admissible blocks of its ancestors
-// (root first) of U_b z_b + sum over its dense blocks of D_b x_sigma, written
-// in the original vertex order.
-__global__ __launch_bounds__(ROW_THREADS) void hmat_rows_kernel(
-    const int32_t *__restrict__ leaf_v0, const int32_t *__restrict__ leaf_m,
-    const int32_t *__restrict__ lb_ptr, const int32_t *__restrict__ lb_idx,
-    const int32_t *__restrict__ ln_ptr, const int32_t *__restrict__ ln_idx,
-    const LrBlock *__restrict__ lr, const float2 *__restrict__ U, const double2 *__restrict__ z,
-    const NearBlock *__restrict__ nb, const float2 *__restrict__ D,
-    const float2 *__restrict__ xt, const int32_t *__restrict__ perm, int64_t N,
-    double2 *__restrict__ yf) {
-    const int lf = blockIdx.x;
-    const int v0 = leaf_v0[lf], m = leaf_m[lf];
-    const int t = threadIdx.x;
-    if (t >= 2 * m) return;
-    const int c = t >= m ? 1 : 0, i = t - c * m;
-    double sr = 0, si = 0;
-    for (int e = lb_ptr[lf]; e < lb_ptr[lf + 1]; e++) {
-        const LrBlock B = lr[lb_idx[e]];
-        const int row = c * B.m + (v0 + i - B.r0);
-        const float2 *u = U + B.uoff + row;
-        const int64_t m2 = 2 * B.m;
-        for (int l = 0; l < B.rank; l++) {
-            const float2 a = u[l * m2];
-            const double2 b = z[B.zoff + l];
-            sr += a.x * b.x - a.y * b.y;
-            si += a.x * b.y + a.y * b.x;
+// Rows of one test leaf: sum over the admissible blocks of its ancestors (root
+// first) of U_b z_b and over its dense blocks of D_b x_sigma.  A leaf's columns
+// (ranks and dense columns, several thousand) are cut into `nsplit` ranges of
+// equal length, a workgroup each; the partial sums are added in range order by
+// hmat_finish_kernel.  A segment is a run of columns of one block: entries at
+// `off` + (row of the leaf) + column * stride, the phi rows `half` further on,
+// times z (kind 0) or xt (kind 1) from `src`.
+//
+// Bound by HBM (U and the dense leaves, read once).  The columns were one
+// serial loop per leaf, a workgroup of 128 threads each: 256 workgroups on the
+// 10 242-vertex sphere, 2.51 ms a launch, 2.69 ms a product.  Cut into ranges,
+// with a column per group of 2m threads and eight loads in flight, the chip is
+// full: 0.41 ms a product (1.2 GB, 3.0 TB/s).
+struct RowSeg {
+    int64_t off, src;
+    int stride, half, cnt, kind;
+};
+constexpr int ROW_THREADS = 256;
+constexpr int ROW_UNROLL = 8;    // loads in flight per thread
+constexpr int ROW_ITEMS = 4096;  // workgroups aimed at (16 per CU)
+constexpr int ROW_MIN_COLS = 128;
+
+template <class VEC>
+__device__ __forceinline__ void row_seg(const RowSeg &g, const float2 *__restrict__ a,
+                                        const VEC *__restrict__ v, int l0, int step, double &sr,
+                                        double &si) {
+    int l = l0;
+    for (; l + (ROW_UNROLL - 1) * step < g.cnt; l += ROW_UNROLL * step) {
+        float2 w[ROW_UNROLL];
+        VEC b[ROW_UNROLL];
+#pragma unroll
+        for (int u = 0; u < ROW_UNROLL; u++) {
+            w[u] = a[(int64_t)(l + u * step) * g.stride];
+            b[u] = v[l + u * step];
+        }
+#pragma unroll
+        for (int u = 0; u < ROW_UNROLL; u++) {
+            sr += (double)w[u].x * b[u].x - (double)w[u].y * b[u].y;
+            si += (double)w[u].x * b[u].y + (double)w[u].y * b[u].x;
         }
     }
-    for (int e = ln_ptr[lf]; e < ln_ptr[lf + 1]; e++) {
-        const NearBlock B = nb[ln_idx[e]];
-        const int64_t m2 = 2 * B.m;
-        const float2 *d = D + B.off + c * B.m + i;
-        for (int q = 0; q < 2 * B.n; q++) {
-            const int dd = q >= B.n ? 1 : 0;
-            const float2 a = d[q * m2], b = xt[dd * N + B.c0 + q - dd * B.n];
-            sr += (double)a.x * b.x - (double)a.y * b.y;
-            si += (double)a.x * b.y + (double)a.y * b.x;
-        }
+    for (; l < g.cnt; l += step) {
+        const float2 w = a[(int64_t)l * g.stride];
+        const VEC b = v[l];
+        sr += (double)w.x * b.x - (double)w.y * b.y;
+        si += (double)w.x * b.y + (double)w.y * b.x;
     }
-    yf[c * N + perm[v0 + i]] = make_double2(sr, si);
 }
 
-// y = yf + near-field CSR x (FP64)
-__global__ __launch_bounds__(256) void hmat_finish_kernel(
-    const double2 *__restrict__ yf, const int32_t *__restrict__ rowptr,
-    const int32_t *__restrict__ col, const double2 *__restrict__ nf, int64_t nnz,
-    const double2 *__restrict__ x, int64_t N, double2 *__restrict__ y) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= N) return;
-    double y1r = yf[i].x, y1i = yf[i].y, y2r = yf[N + i].x, y2i = yf[N + i].y;
-    const double2 *C11 = nf, *C12 = nf + nnz, *C21 = nf + 2 * nnz, *C22 = nf + 3 * nnz;
-    for (int e = rowptr[i]; e < rowptr[i + 1]; e++) {
-        const int j = col[e];
-        const double2 p = x[j], f = x[N + j];
-        const double2 a = C11[e], b = C12[e], c = C21[e], d = C22[e];
-        y1r += a.x * p.x - a.y * p.y + b.x * f.x - b.y * f.y;
-        y1i += a.x * p.y + a.y * p.x + b.x * f.y + b.y * f.x;
-        y2r += c.x * p.x - c.y * p.y + d.x * f.x - d.y * f.y;
-        y2i += c.x * p.y + c.y * p.x + d.x * f.y + d.y * f.x;
+__global__ __launch_bounds__(ROW_THREADS) void hmat_rows_kernel(
+    const int32_t *__restrict__ leaf_m, int nsplit, const int32_t *__restrict__ seg_ptr,
+    const RowSeg *__restrict__ segs, const float2 *__restrict__ U, const float2 *__restrict__ D,
+    const double2 *__restrict__ z, const float2 *__restrict__ xt, double2 *__restrict__ part) {
+    __shared__ double2 sums[ROW_THREADS];
+    const int item = blockIdx.x, rows = 2 * leaf_m[item / nsplit], m = rows / 2;
+    const int groups = ROW_THREADS / rows;   // 2 x leaf <= 128 rows: at least two
+    const int grp = threadIdx.x / rows, row = threadIdx.x - grp * rows;
+    double sr = 0, si = 0;
+    if (grp < groups) {
+        const int c = row >= m ? 1 : 0, i = row - c * m;
+        for (int e = seg_ptr[item]; e < seg_ptr[item + 1]; e++) {
+            const RowSeg g = segs[e];
+            const int64_t at = g.off + i + (c ? g.half : 0);
+            if (g.kind == 0) row_seg(g, U + at, z + g.src, grp, groups, sr, si);
+            else row_seg(g, D + at, xt + g.src, grp, groups, sr, si);
+        }
     }
-    y[i] = make_double2(y1r, y1i);
-    y[N + i] = make_double2(y2r, y2i);
+    sums[threadIdx.x] = make_double2(sr, si);
+    __syncthreads();
+    if (threadIdx.x >= rows) return;
+    for (int q = 1; q < groups; q++) {
+        const double2 o = sums[q * rows + threadIdx.x];
+        sr += o.x;
+        si += o.y;
+    }
+    part[(int64_t)item * (2 * MAX_LEAF) + threadIdx.x] = make_double2(sr, si);
+}
+
+// y = partial sums of the vertex's leaf rows + near-field CSR x (FP64), 16
+// lanes per tree position p (vertex perm[p], leaf and row in it at where[p])
+__global__ __launch_bounds__(256) void hmat_finish_kernel(
+    const double2 *__restrict__ part, int nsplit, const int32_t *__restrict__ leaf_m,
+    const int2 *__restrict__ where, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+    const double2 *__restrict__ nf, int64_t nnz, const double2 *__restrict__ x, int64_t N,
+    double2 *__restrict__ y) {
+    const int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) / NEAR_LANES;
+    const int lane = threadIdx.x % NEAR_LANES;
+    if (p >= N) return;   // (whole groups)
+    const int64_t i = perm[p];
+    const int2 w = where[p];
+    double2 y1 = make_double2(0, 0), y2 = make_double2(0, 0);
+    const double2 *q = part + (int64_t)w.x * nsplit * (2 * MAX_LEAF) + w.y;
+    const int m = leaf_m[w.x];
+    for (int sp = lane; sp < nsplit; sp += NEAR_LANES) {
+        const double2 a = q[(int64_t)sp * (2 * MAX_LEAF)], b = q[(int64_t)sp * (2 * MAX_LEAF) + m];
+        y1.x += a.x;
+        y1.y += a.y;
+        y2.x += b.x;
+        y2.y += b.y;
+    }
+    near_row(lane, i, rowptr, col, nf, nnz, x, N, y1, y2);
+    y1.x = near_sum(y1.x);
+    y1.y = near_sum(y1.y);
+    y2.x = near_sum(y2.x);
+    y2.y = near_sum(y2.y);
+    if (lane == 0) {
+        y[i] = y1;
+        y[N + i] = y2;
+    }
 }
 
 template <bool A_, bool B_, bool C_>
@@ -627,15 +676,17 @@ struct HMatrix {
     DevBuf<float2> U, V;
     DevBuf<NearBlock> nb;
     DevBuf<float2> D;
-    DevBuf<int32_t> leaf_v0, leaf_m, lb_ptr, lb_idx, ln_ptr, ln_idx;
-    int nleaves = 0, nlr = 0;
+    DevBuf<int32_t> leaf_m, seg_ptr;      // per leaf; per (leaf, column range)
+    DevBuf<RowSeg> segs;
+    DevBuf<int2> where;                   // tree position -> (leaf, row)
+    int nleaves = 0, nlr = 0, nsplit = 1;
     int64_t zlen = 0;
-    DevBuf<double2> z, yf;
+    DevBuf<double2> z, part;
     DevBuf<float2> xt;
     int64_t bytes() const {
         return perm.bytes() + lr.bytes() + U.bytes() + V.bytes() + nb.bytes() + D.bytes() +
-               leaf_v0.bytes() + leaf_m.bytes() + lb_ptr.bytes() + lb_idx.bytes() +
-               ln_ptr.bytes() + ln_idx.bytes() + z.bytes() + yf.bytes() + xt.bytes();
+               leaf_m.bytes() + seg_ptr.bytes() + segs.bytes() + where.bytes() + z.bytes() +
+               part.bytes() + xt.bytes();
     }
 };
 
@@ -987,28 +1038,73 @@ std::unique_ptr<HMatrix, HMatDeleter> hmat_build(bem_mesh *m, const NearOperator
     std::vector<std::vector<int32_t>> rows_of(cl.size()), near_of(cl.size());
     for (int b = 0; b < na; b++) rows_of[bl.adm[b].first].push_back(b);
     for (int b = 0; b < nn_; b++) near_of[bl.nearb[b].first].push_back(b);
-    std::vector<int32_t> lv0, lm, lbp{0}, lbi, lnp{0}, lni;
+    std::vector<std::vector<RowSeg>> lsegs;   // per leaf, whole blocks
+    std::vector<int32_t> lm;
+    std::vector<int2> where((size_t)N);
+    int64_t most = 0;   // columns of the longest leaf
     for (int c = 0; c < (int)cl.size(); c++) {
         if (cl[c].child[0] >= 0) continue;
+        const int v0 = cl[c].v0, mm = cl[c].v1 - v0;
         std::vector<int> path;
         for (int a = c; a >= 0; a = cl[a].parent) path.push_back(a);
         std::reverse(path.begin(), path.end());
-        for (int a : path) lbi.insert(lbi.end(), rows_of[a].begin(), rows_of[a].end());
-        lbp.push_back((int32_t)lbi.size());
-        lni.insert(lni.end(), near_of[c].begin(), near_of[c].end());
-        lnp.push_back((int32_t)lni.size());
-        lv0.push_back(cl[c].v0);
-        lm.push_back(cl[c].v1 - cl[c].v0);
+        std::vector<RowSeg> sg;
+        int64_t cols = 0;
+        for (int a : path)
+            for (int b : rows_of[a]) {
+                const LrBlock &B = lr[b];
+                sg.push_back(RowSeg{B.uoff + v0 - B.r0, B.zoff, 2 * B.m, B.m, B.rank, 0});
+                cols += B.rank;
+            }
+        for (int b : near_of[c]) {
+            const NearBlock &B = nbh[b];
+            for (int d = 0; d < 2; d++)   // columns [psi; phi]
+                sg.push_back(RowSeg{B.off + (int64_t)d * B.n * 2 * B.m, d * N + B.c0, 2 * B.m, B.m,
+                                    B.n, 1});
+            cols += 2 * B.n;
+        }
+        for (int i = 0; i < mm; i++) where[v0 + i] = make_int2((int)lsegs.size(), i);
+        lsegs.push_back(std::move(sg));
+        lm.push_back(mm);
+        most = std::max(most, cols);
     }
-    H->nleaves = (int)lv0.size();
-    H->leaf_v0.upload(lv0);
+    H->nleaves = (int)lm.size();
+    // ranges per leaf: enough workgroups to fill the chip, at least
+    // ROW_MIN_COLS columns each in the longest leaf
+    H->nsplit = (int)std::max<int64_t>(
+        1, std::min<int64_t>((ROW_ITEMS + H->nleaves - 1) / H->nleaves, most / ROW_MIN_COLS));
+    std::vector<int32_t> sptr{0};
+    std::vector<RowSeg> segs;
+    for (const auto &sg : lsegs) {
+        int64_t cols = 0;
+        for (const RowSeg &g : sg) cols += g.cnt;
+        const int64_t per = (cols + H->nsplit - 1) / H->nsplit;
+        size_t q = 0;
+        int at = 0;   // columns of segment q already given out
+        for (int sp = 0; sp < H->nsplit; sp++) {
+            for (int64_t left = per; left > 0 && q < sg.size();) {
+                RowSeg g = sg[q];
+                const int take = (int)std::min<int64_t>(left, g.cnt - at);
+                g.off += (int64_t)at * g.stride;
+                g.src += at;
+                g.cnt = take;
+                if (take > 0) segs.push_back(g);
+                left -= take;
+                at += take;
+                if (at == sg[q].cnt) {
+                    q++;
+                    at = 0;
+                }
+            }
+            sptr.push_back((int32_t)segs.size());
+        }
+    }
     H->leaf_m.upload(lm);
-    H->lb_ptr.upload(lbp);
-    H->lb_idx.upload(lbi.empty() ? std::vector<int32_t>{0} : lbi);
-    H->ln_ptr.upload(lnp);
-    H->ln_idx.upload(lni.empty() ? std::vector<int32_t>{0} : lni);
+    H->seg_ptr.upload(sptr);
+    H->segs.upload(segs.empty() ? std::vector<RowSeg>(1) : segs);
+    H->where.upload(where);
     H->z.alloc((size_t)H->zlen);
-    H->yf.alloc((size_t)(2 * N));
+    H->part.alloc((size_t)H->nleaves * H->nsplit * 2 * MAX_LEAF);
     H->xt.alloc((size_t)(2 * N));
     BEM_HIP(hipStreamSynchronize(s));
 
@@ -1062,12 +1158,12 @@ void hmat_apply(HMatrix &H, bem_mesh *m, const NearOperator &nf, const double2 *
     if (H.nlr > 0)
         hipLaunchKernelGGL(hmat_z_kernel, dim3(H.nlr), dim3(256), 0, s, H.lr.p, H.V.p, H.xt.p, N,
                            H.z.p);
-    hipLaunchKernelGGL(hmat_rows_kernel, dim3(H.nleaves), dim3(ROW_THREADS), 0, s, H.leaf_v0.p,
-                       H.leaf_m.p, H.lb_ptr.p, H.lb_idx.p, H.ln_ptr.p, H.ln_idx.p, H.lr.p, H.U.p,
-                       H.z.p, H.nb.p, H.D.p, H.xt.p, H.perm.p, N, H.yf.p);
-    hipLaunchKernelGGL(hmat_finish_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s,
-                       H.yf.p, m->nf_rowptr.p, m->nf_col.p, (const double2 *)nf.vals.p,
-                       m->nf_nnz, x, N, y);
+    hipLaunchKernelGGL(hmat_rows_kernel, dim3((unsigned)(H.nleaves * H.nsplit)), dim3(ROW_THREADS), 0,
+                       s, H.leaf_m.p, H.nsplit, H.seg_ptr.p, H.segs.p, H.U.p, H.D.p, H.z.p, H.xt.p,
+                       H.part.p);
+    hipLaunchKernelGGL(hmat_finish_kernel, dim3((unsigned)((N * NEAR_LANES + 255) / 256)), dim3(256),
+                       0, s, H.part.p, H.nsplit, H.leaf_m.p, H.where.p, H.perm.p, m->nf_rowptr.p,
+                       m->nf_col.p, (const double2 *)nf.vals.p, m->nf_nnz, x, N, y);
     BEM_LAUNCH_CHECK();
 }
 

@@ -147,3 +147,24 @@ def test_hmat_tuning_keys_rejected_out_of_range(P):
     for key, bad in (("hmat.leaf", 65), ("hmat.eta_pct", 5), ("hmat.tol_ppb", 10), ("hmat.kmax", 2)):
         with pytest.raises(P.BemError):
             P.tune_set(key, bad)
+
+
+@pytest.mark.parametrize("leaf,n", [(8, 5), (33, 5), (64, 2), (64, 9)])
+def test_hmat_leaf_sizes(P, leaf, n):
+    """Column ranges of a leaf's rows: leaves of 8 to 64 vertices (16 to 128
+    rows, 16 to 2 column groups), one leaf alone (42 vertices), odd leaf
+    sizes; against the FP64 product at the compression's tolerance."""
+    from bem_inputs import geodesic_sphere
+    mesh = geodesic_sphere(n)
+    N = mesh.n_vertices
+    old = P.tune_get("hmat.leaf")
+    P.tune_set("hmat.leaf", leaf)
+    try:
+        M = P.Mesh.from_inputs(mesh)
+        x = _dev(complex_normal(2 * N, seed=leaf + n))
+        y = P.pmchwt_matvec(M, 2.0, 3.0, 1.5, x, precision="fp32_hmat").cpu().numpy()
+    finally:
+        P.tune_set("hmat.leaf", old)
+    ref = P.pmchwt_matvec(M, 2.0, 3.0, 1.5, x, precision="fp64").cpu().numpy()
+    for sl in (slice(0, N), slice(N, 2 * N)):
+        assert _rel(y[sl], ref[sl]) <= TOL
