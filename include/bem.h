@@ -492,8 +492,9 @@ int bem_profile_read(const char *kernel, double *total_ms, int64_t *launches);
 
 /* Process-wide default launch parameters, used for shapes without an
  * autotuned entry:
- *   "farfield.multi_max"  right-hand sides sharing one pair-kernel launch on
- *                         the FP32 matrix-free path: 1, 2 or 4 (default 4)
+ *   "farfield.multi_max"  1: one right-hand side per pair-kernel launch; 2 or 4:
+ *                         launches shared by up to 32 (FP32) or 8 (FP64)
+ *                         (default 4)
  *   "farfield.block"      test triangles per pair-kernel workgroup: 64, 128
  *                         or 256 (default 256)
  *   "farfield.symmetric"  1: a single FP32 right-hand side evaluates every

@@ -19,7 +19,7 @@ OUT_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libbem.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["api.cpp", "mesh.cpp", "quadrature.cpp", "farfield.hip",
+SOURCES = ["api.cpp", "mesh.cpp", "quadrature.cpp", "farfield.hip", "batch.hip",
            "nearfield.hip", "rhs.hip", "sparse_ldl.cpp", "osrc.cpp",
            "osrc_kernels.hip", "blas.hip", "dense.hip", "solve.cpp", "probe.hip",
            "server.cpp", "tune.cpp", "field.hip", "noalloc.hip", "hmat.hip"]

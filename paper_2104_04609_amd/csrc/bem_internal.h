@@ -139,6 +139,8 @@ struct NearOperator {
     // filled on first use)
     mutable DevBuf<float> itab32;
     mutable DevBuf<double> itab64;
+    mutable DevBuf<float> dtab32;    // the same for the batch kernel
+    mutable DevBuf<double> dtab64;
 };
 
 // Interior materials of the objects when they differ (Sec. 2.7, several
@@ -300,7 +302,7 @@ namespace bem {
 
 // Process-wide default launch parameters (bem_tune_set / bem_tune_get).
 struct Tuning {
-    std::atomic<int> farfield_multi_max{4};   // right-hand sides per pair-kernel launch
+    std::atomic<int> farfield_multi_max{4};   // >= 2: pair-kernel launches shared by several vectors
     std::atomic<int> farfield_block{256};     // test triangles per pair-kernel workgroup
     std::atomic<int> farfield_symmetric{1};   // FP32 single vector: each separated pair once
     std::atomic<int> farfield_sym_round_mib{4096};   // symmetric kernel: sigma partials per launch
@@ -327,7 +329,7 @@ Tuning &tuning();
 // autotuned entry (tune.cpp) or the defaults above.
 struct TuneEntry {
     int block = 256;           // test triangles per pair-kernel workgroup: 64, 128, 256
-    int multi = 4;             // right-hand sides per pair-kernel launch: 1, 2, 4
+    int multi = 4;             // 1: one right-hand side per pair-kernel launch; 2, 4: shared
     int gemm_min = 24;         // MFMA product from this many right-hand sides
     int skinny_min = 24;       // below gemm_min: skinny MFMA product from this many, else multi-vector GEMV
     int path = -1;             // FP32 solves: -1 no preference, 0 matrix-free, 1 assembled
@@ -341,8 +343,8 @@ bool tune_find(int64_t T, int R, TuneEntry *e);
 void farfield_apply(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
                     double rho, const double2 *x, double2 *y, int precision,
                     hipStream_t s, int block = 0);
-// y_r = B x_r for R right-hand sides ([R][2N]); FP32 shares each kernel
-// evaluation among up to 4 right-hand sides
+// y_r = B x_r for R right-hand sides ([R][2N]); two or more share each kernel
+// evaluation
 // Launch parameters: tune_lookup(T, R) unless `forced` is given.
 void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
                           double rho, const double2 *x, double2 *y, int R, int precision,
@@ -350,6 +352,13 @@ void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, doubl
 // device scratch (source records, split partials, triangle rows) that
 // farfield_apply_batch needs for this precision, wavenumber pair and R
 int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, double2 k1, int R);
+// batch.hip: y_r = B x_r for up to farfield_mx_max(precision) vectors
+// ([nr][2N]), every triangle pair evaluated once for all of them; device
+// scratch of a batch of R vectors
+int farfield_mx_max(int precision);
+void farfield_mx_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const double2 *x, double2 *y,
+                       int nr, int precision, hipStream_t s);
+int64_t farfield_mx_bytes(const bem_mesh *m, int precision, double2 k0, double2 k1, int R);
 // nearfield.hip
 // s1 = +1: near field of the permuted PMCHWT operator; s1 = -1: of the
 // Mueller operator on the same unknowns (interior terms negated, P1 mass

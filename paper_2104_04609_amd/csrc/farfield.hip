@@ -836,8 +836,9 @@ void farfield_sym_kernel(
 
 // ----------------------------------------- multi-right-hand-side pair kernel
 // NR right-hand sides share every kernel evaluation (geometry, phases,
-// G_V, G_W, G_N, F); only the accumulations are per right-hand side.  FP32,
-// phases below 256 revolutions.  dyn: [NR][T][DYN_STRIDE]; partial of
+// G_V, G_W, G_N, F); only the accumulations are per right-hand side.  For two
+// vectors (from three on the batch kernel on the matrix cores is faster).
+// FP32 phases below 256 revolutions.  dyn: [NR][T][DYN_STRIDE]; partial of
 // right-hand side r at partial + r nsplit T (ROW_STRIDE + 6), same layout
 // as the single-vector kernel.  Per-tile FP64 sums are accumulated in place
 // in the thread's own partial slots.
@@ -1588,17 +1589,19 @@ const SymPlan &sym_plan_for(const bem_mesh *m, const FarPlan &fp) {
 
 }   // namespace
 
-// right-hand sides per multi-vector pair-kernel launch
-constexpr int FF_MULTI_MAX = 4;
-constexpr int FF_MULTI_MAX_FP64 = 2;
+// Vectors from which the batch kernel is used: its time hardly depends on the
+// number of vectors.  6 252 vertices, ms: FP32 12.5 for 2 to 8 vectors, 6.1 each
+// alone, 11.5 for two sharing a launch; FP64 27.9, 16.8 and 24.3.
+constexpr int FF_BATCH_MIN = 3;
 
-// Upper bound over every block size and vectors-per-launch choice, so that
+// Upper bound over every block size and the batch kernel's launches, so that
 // it holds whatever the tuning table says.
 int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, double2 k1, int R) {
     const int64_t T = m->T;
     const bool f32 = precision == BEM_FP32;
     const int64_t rb = f32 ? 4 : 8;
-    int64_t dyn = T * DYN_STRIDE * rb, part = 0;
+    const int64_t dyn = (R < 2 ? 1 : 2) * T * DYN_STRIDE * rb;
+    int64_t part = 0;
     for (int blk : {64, 128, 256}) {
         const FarPlan p = far_plan(m, precision, k0, k1, blk);
         part = std::max(part, (int64_t)p.nsplit * T * (ROW_STRIDE + 6) * 8);
@@ -1608,16 +1611,11 @@ int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, dou
                                       (int64_t)sp.items.size() * 4);
         }
         if (R < 2 || (f32 && p.fr)) continue;
-        for (int nr : {2, 4}) {
-            if (nr > R || nr > (f32 ? FF_MULTI_MAX : FF_MULTI_MAX_FP64)) continue;
-            const void *k = f32 ? (nr == 4 ? multi_kernel<float, 4>(p.code)
-                                           : multi_kernel<float, 2>(p.code))
-                                : multi_kernel<double, 2>(p.code);
-            const int ns = farfield_splits((int)T, far_slots(k, blk, 0), blk);
-            dyn = std::max(dyn, (int64_t)nr * T * DYN_STRIDE * rb);
-            part = std::max(part, (int64_t)nr * ns * T * (ROW_STRIDE + 6) * 8);
-        }
+        const void *k = f32 ? multi_kernel<float, 2>(p.code) : multi_kernel<double, 2>(p.code);
+        part = std::max(part, (int64_t)2 * farfield_splits((int)T, far_slots(k, blk, 0), blk) * T *
+                                  (ROW_STRIDE + 6) * 8);
     }
+    if (R >= FF_BATCH_MIN) part = std::max(part, farfield_mx_bytes(m, precision, k0, k1, R));
     return dyn + part + T * ROW_STRIDE * 8;
 }
 
@@ -1780,20 +1778,25 @@ void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, doubl
     const TuneEntry te = forced ? *forced : tune_lookup(m->T, R);
     const int blk = valid_block(te.block);
     const FarPlan plan = far_plan(m, precision, k0, nf.k1_plan, blk);
+    // vectors sharing every kernel evaluation (FP32 phases are not reduced there,
+    // so they stay below 256 revolutions)
     int r0 = 0;
-    const int mm = te.multi;
-    if (precision == BEM_FP32 && !plan.fr && mm >= 2) {
-        if (mm >= 4)
-            for (; R - r0 >= 4; r0 += 4)
-                farfield_multi_apply<float, 4>(m, nf, k0, k1, rho, plan.code, blk, x + r0 * n2,
-                                               y + r0 * n2, s);
-        for (; R - r0 >= 2; r0 += 2)
-            farfield_multi_apply<float, 2>(m, nf, k0, k1, rho, plan.code, blk, x + r0 * n2,
-                                           y + r0 * n2, s);
-    } else if (precision == BEM_FP64 && mm >= 2) {
-        for (; R - r0 >= 2; r0 += 2)
-            farfield_multi_apply<double, 2>(m, nf, k0, k1, rho, plan.code, blk, x + r0 * n2,
-                                            y + r0 * n2, s);
+    if (te.multi >= 2 && !(precision == BEM_FP32 && plan.fr)) {
+        const int most = farfield_mx_max(precision);
+        while (R - r0 >= FF_BATCH_MIN) {
+            const int nr = std::min(most, R - r0);
+            farfield_mx_apply(m, nf, k0, x + r0 * n2, y + r0 * n2, nr, precision, s);
+            r0 += nr;
+        }
+        if (R - r0 == 2) {
+            const double2 *xr = x + r0 * n2;
+            double2 *yr = y + r0 * n2;
+            if (precision == BEM_FP32)
+                farfield_multi_apply<float, 2>(m, nf, k0, k1, rho, plan.code, blk, xr, yr, s);
+            else
+                farfield_multi_apply<double, 2>(m, nf, k0, k1, rho, plan.code, blk, xr, yr, s);
+            r0 += 2;
+        }
     }
     for (; r0 < R; r0++)
         farfield_apply(m, nf, k0, k1, rho, x + r0 * n2, y + r0 * n2, precision, s, blk);

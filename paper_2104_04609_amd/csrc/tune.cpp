@@ -178,7 +178,7 @@ TuneEntry autotune(bem_mesh *m, double2 k0, double2 k1, double rho, int R, int e
     TuneEntry best = tune_lookup(m->T, R);
     best.t_mf = 1e300;
     for (int blk : {64, 128, 256})
-        for (int mm : {1, 2, 4}) {
+        for (int mm : {1, 2}) {   // one vector per launch, or shared launches
             if (mm > 1 && mm > R) continue;
             TuneEntry c = best;
             c.block = blk;
