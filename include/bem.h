@@ -497,7 +497,7 @@ int bem_profile_read(const char *kernel, double *total_ms, int64_t *launches);
  *                         (default 4)
  *   "farfield.block"      test triangles per pair-kernel workgroup: 64, 128
  *                         or 256 (default 256)
- *   "farfield.symmetric"  1: a single FP32 right-hand side evaluates every
+ *   "farfield.symmetric"  1: a single right-hand side evaluates every
  *                         separated triangle pair once and adds it to the
  *                         rows of both triangles (the kernels of V, K, K'
  *                         and D in Maue form depend on the points only

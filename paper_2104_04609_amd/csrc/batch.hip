@@ -114,8 +114,8 @@ template <> struct Mx<double> {
 __device__ __forceinline__ float fmaC(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmaC(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// sin and cos of 2 pi t: FP32 phases stay below 256 revolutions here, inside
-// which the hardware functions reduce exactly
+// sin and cos of the phase t (phase units): FP32 phases stay below 256
+// revolutions here, inside which the hardware functions reduce exactly
 __device__ __forceinline__ void sc_rev(float t, float &s, float &c, const double2 *) {
     s = __builtin_amdgcn_sinf(t);
     c = __builtin_amdgcn_cosf(t);
@@ -138,22 +138,9 @@ template <class R> __device__ __forceinline__ R wb_at(int k) {
     else return kWB64[k];
 }
 
-// 2^x for x <= 0 (decay of lossy media).  FP64: x = n / 64 + f, a table of
-// 2^(k / 64) and the series of 2^f, |f ln 2| <= 0.0055 (remainder 4e-17).
-constexpr int XTAB = 64;
+// 2^x for x <= 0 (decay of lossy media)
 __device__ __forceinline__ float decay(float x, const double *) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ double decay(double x, const double *tab) {
-    x = fmax(x, -1100.0);   // (below the smallest number: 0)
-    const double n = __builtin_rint(64.0 * x);
-    const double f = __builtin_fma(-0.015625, n, x) * 0.69314718055994530941723212145818;
-    double p = __builtin_fma(f, 1.0 / 120.0, 1.0 / 24.0);
-    p = __builtin_fma(p, f, 1.0 / 6.0);
-    p = __builtin_fma(p, f, 0.5);
-    p = __builtin_fma(p, f, 1.0);
-    p = __builtin_fma(p, f, 1.0);
-    const int k = (int)n;
-    return __builtin_ldexp(p * tab[k & (XTAB - 1)], k >> 6);
-}
+__device__ __forceinline__ double decay(double x, const double *tab) { return decay64(x, tab); }
 
 // x [nr][2N] -> xt [N][2][cols], vector r in columns 2r (re) and 2r + 1 (im),
 // zeros beyond nr
@@ -509,13 +496,12 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
     __shared__ int32_t gi[BT_TILE * 4];
     __shared__ double gt[BT_TILE * TST_STRIDE];   // areas and curls
     __shared__ double2 etab[256];
-    __shared__ double xtab[XTAB];
+    __shared__ double xtab[DECAY_TAB];
     __shared__ double cu[W * BT_TAU * 9];   // curls of the test triangles
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 15, kq = lane >> 4;
     DM<R>::fill_table(etab);
-    if (CK0 || CK1)
-        for (int n = threadIdx.x; n < XTAB; n += BT_THREADS) xtab[n] = ::exp2(n * 0.015625);
+    if (CK0 || CK1) decay_table(xtab);
     for (int n = threadIdx.x; n < W * BT_TAU * 9; n += BT_THREADS) {
         const int t = min((int)blockIdx.x * W * BT_TAU + n / 9, T - 1);
         cu[n] = tst[(int64_t)TST_STRIDE * t + 1 + n % 9];

@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "bem_internal.h"
+#include "fp64_math.h"
 
 namespace bem {
 namespace entries {
@@ -33,7 +34,8 @@ __host__ __device__ constexpr double qb(int i, int a) {
 
 // interior coefficients of one object (several objects: a per-object table)
 template <class R> struct DIntT {
-    R krev1, k1r, k1i, kdec1, rho, irho, n10r, n10i;
+    R krev1;   // Re k_1 / (2 pi) in phase units
+    R k1r, k1i, kdec1, rho, irho, n10r, n10i;
     R ns1;   // -s_1 (interior sign: +1 PMCHWT, -1 Mueller)
 };
 template <class R> struct DCoefT {
@@ -45,10 +47,8 @@ __device__ __forceinline__ float fmaR(float a, float b, float c) { return __buil
 __device__ __forceinline__ double fmaR(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // Arithmetic per precision.  FP32: hardware sin/cos (in revolutions),
-// 1/sqrt and exp2; stored as complex64.  FP64: sin/cos of 2 pi t from a table
-// of e^{2 pi i n/256} and the Taylor series of the remainder (|2 pi f| <=
-// pi/256, terms beyond x^6 below 4e-18), 1/sqrt from the hardware estimate and
-// two Newton steps; complex128.
+// 1/sqrt and exp2; stored as complex64.  FP64: fp64_math.h (phases in 256ths of
+// a revolution); complex128.
 template <class R> struct DM;
 template <> struct DM<float> {
     using C = float2;
@@ -64,32 +64,12 @@ template <> struct DM<float> {
 };
 template <> struct DM<double> {
     using C = double2;
-    static __device__ __forceinline__ void fill_table(double2 *tab) {
-        for (int n = threadIdx.x; n < 256; n += blockDim.x) {
-            double sn, cs;
-            ::sincos(n * (6.283185307179586476925286766559 / 256.0), &sn, &cs);
-            tab[n] = make_double2(cs, sn);
-        }
-    }
-    static __device__ __forceinline__ void sincos(double t, double &s, double &c,
+    static __device__ __forceinline__ void fill_table(double2 *tab) { phase_table(tab); }
+    static __device__ __forceinline__ void sincos(double u, double &s, double &c,
                                                   const double2 *tab) {
-        const double n = __builtin_rint(256.0 * t);
-        const double x = __builtin_fma(-0.00390625, n, t) * 6.283185307179586476925286766559;
-        const double x2 = x * x;
-        const double sn = __builtin_fma(__builtin_fma(x2, 1.0 / 120.0, -1.0 / 6.0), x2, 1.0) * x;
-        const double cs =
-            __builtin_fma(__builtin_fma(__builtin_fma(x2, -1.0 / 720.0, 1.0 / 24.0), x2, -0.5), x2, 1.0);
-        const double2 e = tab[((int64_t)n) & 255];
-        c = __builtin_fma(e.x, cs, -e.y * sn);
-        s = __builtin_fma(e.y, cs, e.x * sn);
+        sincos_256(u, s, c, tab);
     }
-    static __device__ __forceinline__ double rsq(double x) {
-        double y = __builtin_amdgcn_rsq(x);
-        const double h = 0.5 * x;
-        y = y * __builtin_fma(-h * y, y, 1.5);
-        y = y * __builtin_fma(-h * y, y, 1.5);
-        return y;
-    }
+    static __device__ __forceinline__ double rsq(double x) { return rsqrt64(x); }
     static __device__ __forceinline__ double exp2(double x) { return ::exp2(x); }
     static __device__ __forceinline__ double2 mk(double a, double b) { return make_double2(a, b); }
 };
@@ -263,7 +243,7 @@ template <class R> inline DIntT<R> make_dint(double2 k0, double2 k1, double rho,
     const double inv2pi = 0.15915494309189533576888376337251;
     const double log2e = 1.4426950408889634073599246810019;
     DIntT<R> c;
-    c.krev1 = (R)(k1.x * inv2pi);
+    c.krev1 = (R)(k1.x * inv2pi * phase_unit<R>());
     c.k1r = (R)k1.x;
     c.k1i = (R)k1.y;
     c.kdec1 = (R)(-k1.y * log2e);
@@ -291,7 +271,7 @@ template <class R> inline DCoefT<R> make_dcoef(double2 k0, const NearOperator &n
     const double inv2pi = 0.15915494309189533576888376337251;
     const double log2e = 1.4426950408889634073599246810019;
     DCoefT<R> c;
-    c.krev0 = (R)(k0.x * inv2pi);
+    c.krev0 = (R)(k0.x * inv2pi * phase_unit<R>());
     c.k0r = (R)k0.x;
     c.k0i = (R)k0.y;
     c.kdec0 = (R)(-k0.y * log2e);

@@ -34,11 +34,12 @@
 #include <functional>
 #include <map>
 #include <mutex>
-#include <queue>
 #include <type_traits>
 #include <utility>
 
 #include "bem_internal.h"
+#include "fp64_math.h"
+#include "near_row.h"
 
 namespace bem {
 
@@ -72,6 +73,12 @@ __constant__ float kQWB[18] = {BEM_QWB_ROW(0), BEM_QWB_ROW(1), BEM_QWB_ROW(2),
                                BEM_QWB_ROW(3), BEM_QWB_ROW(4), BEM_QWB_ROW(5)};
 #undef BEM_QW2_ROW
 #undef BEM_QWB_ROW
+// the same in FP64: w_j, w_j phi_a(y_j)
+#define BEM_QWB_ROW(j) qw(j) * qb(j, 0), qw(j) * qb(j, 1), qw(j) * qb(j, 2)
+__constant__ double kQW64[6] = {qw(0), qw(1), qw(2), qw(3), qw(4), qw(5)};
+__constant__ double kQWB64[18] = {BEM_QWB_ROW(0), BEM_QWB_ROW(1), BEM_QWB_ROW(2),
+                                  BEM_QWB_ROW(3), BEM_QWB_ROW(4), BEM_QWB_ROW(5)};
+#undef BEM_QWB_ROW
 
 // ---------------------------------------------------------------- math
 template <class R> struct Math;
@@ -93,66 +100,12 @@ template <> struct Math<float> {
 };
 
 template <> struct Math<double> {
-    // sin/cos of 2 pi t for moderate |t|: t = n/4 + f, |f| <= 1/8, then
-    // Taylor series of sin and cos on [-pi/4, pi/4] (truncation < 5e-17) and
-    // the quadrant rotation by n.
-    template <bool FR>
-    static __device__ __forceinline__ void sincos_rev(double t, double &s, double &c) {
-        double n = __builtin_rint(4.0 * t);
-        double f = __builtin_fma(-0.25, n, t);
-        double x = f * 6.283185307179586476925286766559;
-        double x2 = x * x;
-        double ps = 1.0 / 1307674368000.0;           // 1/15!
-        ps = __builtin_fma(ps, -x2, 1.0 / 6227020800.0);    // 1/13!
-        ps = __builtin_fma(ps, -x2, 1.0 / 39916800.0);      // 1/11!
-        ps = __builtin_fma(ps, -x2, 1.0 / 362880.0);        // 1/9!
-        ps = __builtin_fma(ps, -x2, 1.0 / 5040.0);          // 1/7!
-        ps = __builtin_fma(ps, -x2, 1.0 / 120.0);           // 1/5!
-        ps = __builtin_fma(ps, -x2, 1.0 / 6.0);             // 1/3!
-        ps = __builtin_fma(ps, -x2, 1.0);
-        double sn = ps * x;
-        double pc = 1.0 / 20922789888000.0;          // 1/16!
-        pc = __builtin_fma(pc, -x2, 1.0 / 87178291200.0);   // 1/14!
-        pc = __builtin_fma(pc, -x2, 1.0 / 479001600.0);     // 1/12!
-        pc = __builtin_fma(pc, -x2, 1.0 / 3628800.0);       // 1/10!
-        pc = __builtin_fma(pc, -x2, 1.0 / 40320.0);         // 1/8!
-        pc = __builtin_fma(pc, -x2, 1.0 / 720.0);           // 1/6!
-        pc = __builtin_fma(pc, -x2, 1.0 / 24.0);            // 1/4!
-        pc = __builtin_fma(pc, -x2, 0.5);                   // 1/2!
-        double cs = __builtin_fma(pc, -x2, 1.0);
-        int q = ((int)n) & 3;
-        double s0 = (q & 1) ? cs : sn;
-        double c0 = (q & 1) ? sn : cs;
-        s = (q & 2) ? -s0 : s0;
-        c = ((q + 1) & 2) ? -c0 : c0;
-    }
-    // sin/cos of 2 pi t with a table of e^{2 pi i n / 256}: t = n/256 + f,
-    // |f| <= 1/512, so |2 pi f| <= 0.0123 and short Taylor series suffice
-    // (truncation x^7/7! < 4e-18, x^8/8! < 2e-20); then one complex product.
-    static __device__ __forceinline__ void sincos_tab(double t, double &s, double &c,
+    // sin/cos of the phase u (in 256ths of a revolution)
+    static __device__ __forceinline__ void sincos_tab(double u, double &s, double &c,
                                                       const double2 *tab) {
-        const double n = __builtin_rint(256.0 * t);
-        const double f = __builtin_fma(-0.00390625, n, t);
-        const double x = f * 6.283185307179586476925286766559;
-        const double x2 = x * x;
-        double ps = __builtin_fma(x2, 1.0 / 120.0, -1.0 / 6.0);
-        ps = __builtin_fma(ps, x2, 1.0);
-        const double sn = ps * x;
-        double pc = __builtin_fma(x2, -1.0 / 720.0, 1.0 / 24.0);
-        pc = __builtin_fma(pc, x2, -0.5);
-        const double cs = __builtin_fma(pc, x2, 1.0);
-        const double2 e = tab[((int)n) & 255];
-        c = __builtin_fma(e.x, cs, -e.y * sn);
-        s = __builtin_fma(e.y, cs, e.x * sn);
+        sincos_256(u, s, c, tab);
     }
-    // 1/sqrt(x): hardware estimate refined by two Newton steps
-    static __device__ __forceinline__ double rsq(double x) {
-        double y = __builtin_amdgcn_rsq(x);
-        double h = 0.5 * x;
-        y = y * __builtin_fma(-h * y, y, 1.5);
-        y = y * __builtin_fma(-h * y, y, 1.5);
-        return y;
-    }
+    static __device__ __forceinline__ double rsq(double x) { return rsqrt64(x); }
     static __device__ __forceinline__ double exp2(double x) { return ::exp2(x); }
 };
 
@@ -166,7 +119,7 @@ __device__ __forceinline__ double fmac(double a, double b, double c) {
 // Interior coefficients of one object (material k_1, rho of that object).
 constexpr int INT_COEFS = 9;
 template <class R> struct Int {
-    R krev1;                 // Re k_1 / (2 pi)
+    R krev1;                 // Re k_1 / (2 pi), phase units
     R k1r, k1i;              // k_1
     R kdec1;                 // -Im k_1 * log2(e)
     R rho, irho;
@@ -178,7 +131,7 @@ template <class R> struct Int {
 // objects take the interior part of each trial triangle's object from a
 // per-object table instead of `in`.
 template <class R> struct Coef {
-    R krev0;                 // Re k_0 / (2 pi)
+    R krev0;                 // Re k_0 / (2 pi), phase units
     R k0r, k0i;              // k_0
     R kdec0;                 // -Im k_0 * log2(e)
     R n0r, n0i;              // k_0^2
@@ -262,11 +215,7 @@ void farfield_kernel(
     const int tau = blockIdx.x * nthr + threadIdx.x;
     const int split = blockIdx.y;
     if constexpr (!F32) {
-        for (int n = threadIdx.x; n < 256; n += nthr) {
-            double sn, cs;
-            MT::template sincos_rev<true>(n * 0.00390625, sn, cs);
-            etab[n] = make_double2(cs, sn);
-        }
+        phase_table(etab);
         // the first tile's barrier orders these writes before any read
     }
     const int s_begin = split * split_len;
@@ -834,49 +783,74 @@ void farfield_sym_kernel(
     for (int k = 0; k < SIG_VALS; k++) out[k] = sums[k * nthr + threadIdx.x];
 }
 
-// ----------------------------------------- multi-right-hand-side pair kernel
-// NR right-hand sides share every kernel evaluation (geometry, phases,
-// G_V, G_W, G_N, F); only the accumulations are per right-hand side.  For two
-// vectors (from three on the batch kernel on the matrix cores is faster).
-// FP32 phases below 256 revolutions.  dyn: [NR][T][DYN_STRIDE]; partial of
-// right-hand side r at partial + r nsplit T (ROW_STRIDE + 6), same layout
-// as the single-vector kernel.  Per-tile FP64 sums are accumulated in place
-// in the thread's own partial slots.
-template <int NR> constexpr int srcm() { return GEO_STRIDE + 4 + NR * DYN_STRIDE; }
-
-template <class R, int NR> constexpr int multi_waves() {
-    return std::is_same<R, double>::value || NR >= 4 ? 1 : 2;
+// ------------------------------------------- symmetric pair kernel, FP64
+// The same sums with FP64 values.  Bound by FP64 VALU issue: about 120
+// instructions per unordered point pair against 2 x 94 of the ordered kernel.
+// Registers are what limits it (two wavefronts per SIMD at 256): F (y - x).n_y
+// is formed per point pair and serves both rows, so that neither its sums over
+// the trial points nor the test-side weights are kept; the curl data of the
+// test triangle and its curl sums live in LDS.  A wave's 18 sums over its lanes
+// are halved pairwise by lane swaps (18 -> 9 -> 5 values) before the steps
+// within 16 lanes: 102 instructions instead of 324.
+__device__ __forceinline__ double swap_add32(double a, double b) {
+    // lanes 0..31: a(l) + a(l + 32); lanes 32..63: b(l - 32) + b(l)
+    const long long x = __builtin_bit_cast(long long, a), y = __builtin_bit_cast(long long, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false,
+                                                     false);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __builtin_bit_cast(double, (long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {
+    // rows of 16 lanes: even rows a(row) + a(row + 1), odd rows b(row - 1) + b(row)
+    const long long x = __builtin_bit_cast(long long, a), y = __builtin_bit_cast(long long, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false,
+                                                     false);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __builtin_bit_cast(double, (long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_add64(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return v + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double row_sum64(double v) {   // over 16 lanes, on all of them
+    v = dpp_add64<0x128>(v);   // row_ror:8
+    v = dpp_add64<0x124>(v);   // row_ror:4
+    v = dpp_add64<0x4E>(v);    // quad_perm [2,3,0,1]
+    return dpp_add64<0xB1>(v); // quad_perm [1,0,3,2]
 }
 
-template <class R, bool CK0, bool CK1, bool MULTI, int NR>
-__global__ __launch_bounds__(FF_BLOCK) __attribute__((amdgpu_waves_per_eu(multi_waves<R, NR>())))
-void farfield_multi_kernel(
-    const R *__restrict__ geo, const R *__restrict__ dyn,
+template <bool CK0, bool CK1, bool MULTI>
+__global__ __launch_bounds__(FF_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
+void farfield_sym64_kernel(
+    const double *__restrict__ geo, const double *__restrict__ dyn,
     const int32_t *__restrict__ tobj, const int32_t *__restrict__ tri, int T,
-    int split_len, Coef<R> cf, const Int<R> *__restrict__ itab,
-    double *__restrict__ partial) {
-    using MT = Math<R>;
-    // FP32 phases are below 256 revolutions on this path; FP64 always reduces
-    constexpr bool FRM = std::is_same<R, double>::value;
-    constexpr int SM = srcm<NR>();
-    constexpr int OBJ = GEO_STRIDE, VID = GEO_STRIDE + 1, DYN0 = GEO_STRIDE + 4;
-    __shared__ R tile[FF_TILE * SM];
-    __shared__ double2 etab[FRM ? 256 : 1];
+    const int32_t *__restrict__ items, int chunk_len, Coef<double> cf,
+    const Int<double> *__restrict__ itab, double *__restrict__ ptau, double *__restrict__ psig,
+    int64_t sig_base) {
+    using R = double;
+    __shared__ R tile[FF_TILE * SRC];
+    __shared__ double2 etab[256];
+    __shared__ double xtab[DECAY_TAB];
+    // dynamic: [6][threads] curl of the test triangle as trial triangle, [6][threads]
+    // its rows' curl sums, [waves][FF_TILE][SIG_VALS] the waves' sums for sigma
+    extern __shared__ double sums[];
     const int nthr = blockDim.x;
-    const int tau = blockIdx.x * nthr + threadIdx.x;
-    if constexpr (FRM) {
-        for (int n = threadIdx.x; n < 256; n += nthr) {
-            double sn, cs;
-            MT::template sincos_rev<true>(n * 0.00390625, sn, cs);
-            etab[n] = make_double2(cs, sn);
-        }
-        // the first tile's barrier orders these writes before any read
-    }
-    const int split = blockIdx.y;
-    const int s_begin = split * split_len;
-    const int s_end = min(T, s_begin + split_len);
+    R *own = sums, *curl = sums + 6 * nthr, *sig = sums + 12 * nthr;
+    phase_table(etab);
+    if (CK0 || CK1) decay_table(xtab);
+    // (the first tile's barrier orders these writes before any read)
+    const int b = items[3 * blockIdx.x], c = items[3 * blockIdx.x + 1],
+              canon = items[3 * blockIdx.x + 2];
+    const int tau = b * nthr + threadIdx.x;
+    const int lo = b * nthr + c * chunk_len;
+    const int hi = min(T, lo + chunk_len);
     const bool active = tau < T;
     const int tt = active ? tau : 0;
+    const int wave = threadIdx.x >> 6;
 
     R px[6], py[6], pz[6];
     for (int i = 0; i < 6; i++) {
@@ -888,198 +862,238 @@ void farfield_multi_kernel(
             ntz = geo[GEO_STRIDE * tt + 20], ct = geo[GEO_STRIDE * tt + 21];
     const R ot = MULTI ? (R)tobj[tt] : (R)0;
     const R tv0 = (R)tri[3 * tt], tv1 = (R)tri[3 * tt + 1], tv2 = (R)tri[3 * tt + 2];
-
-    R a1r[NR][6], a1i[NR][6], a2r[NR][6], a2i[NR][6], Ar[NR][3], Ai[NR][3];
-    for (int r = 0; r < NR; r++) {
-        for (int i = 0; i < 6; i++) a1r[r][i] = a1i[r][i] = a2r[r][i] = a2i[r][i] = 0;
-        for (int c = 0; c < 3; c++) Ar[r][c] = Ai[r][c] = 0;
+    // tau as a trial triangle: s_psi, s_phi at its points
+    R tspr[6], tspi[6], tsfr[6], tsfi[6];
+    for (int i = 0; i < 6; i++) {
+        tspr[i] = dyn[DYN_STRIDE * tt + 2 * i];
+        tspi[i] = dyn[DYN_STRIDE * tt + 2 * i + 1];
+        tsfr[i] = dyn[DYN_STRIDE * tt + 12 + 2 * i];
+        tsfi[i] = dyn[DYN_STRIDE * tt + 12 + 2 * i + 1];
     }
-    const int64_t rstride = (int64_t)gridDim.y * T * (ROW_STRIDE + 6);
-    double *out = partial + ((int64_t)split * T + tau) * ROW_STRIDE;
-    double *outA = partial + (int64_t)gridDim.y * T * ROW_STRIDE + ((int64_t)split * T + tau) * 6;
-    bool first = true;
-    auto flush = [&]() {
-        for (int r = 0; r < NR; r++) {
-            double v[ROW_STRIDE + 6];
-            for (int a = 0; a < 3; a++) {
-                double r1r = 0, r1i = 0, r2r = 0, r2i = 0;
-                for (int i = 0; i < 6; i++) {
-                    double wb = qw(i) * qb(i, a);
-                    r1r += wb * (double)a1r[r][i];
-                    r1i += wb * (double)a1i[r][i];
-                    r2r += wb * (double)a2r[r][i];
-                    r2i += wb * (double)a2i[r][i];
-                }
-                v[2 * a] = r1r;
-                v[2 * a + 1] = r1i;
-                v[6 + 2 * a] = r2r;
-                v[6 + 2 * a + 1] = r2i;
-            }
-            for (int c = 0; c < 3; c++) {
-                v[ROW_STRIDE + 2 * c] = (double)Ar[r][c];
-                v[ROW_STRIDE + 2 * c + 1] = (double)Ai[r][c];
-                Ar[r][c] = Ai[r][c] = 0;
-            }
-            for (int i = 0; i < 6; i++) a1r[r][i] = a1i[r][i] = a2r[r][i] = a2i[r][i] = 0;
-            if (active) {
-                double *o = out + r * rstride, *oA = outA + r * rstride;
-                for (int c = 0; c < ROW_STRIDE; c++) o[c] = first ? v[c] : o[c] + v[c];
-                for (int c = 0; c < 6; c++) oA[c] = first ? v[ROW_STRIDE + c] : oA[c] + v[ROW_STRIDE + c];
-            }
+    for (int k = 0; k < 6; k++) {
+        own[k * nthr + threadIdx.x] = dyn[DYN_STRIDE * tt + 24 + k];
+        curl[k * nthr + threadIdx.x] = 0;
+    }
+    R a1r[6], a1i[6], a2r[6], a2i[6];
+    for (int i = 0; i < 6; i++) a1r[i] = a1i[i] = a2r[i] = a2i[i] = 0;
+    // rows of sigma of one tile: the waves' sums in wave order
+    const int nw = nthr >> 6;
+    double *psb = psig + (sym_sig_off(b, T, nthr) - sig_base - (int64_t)b * nthr) * SIG_VALS;
+    auto combine = [&](int tb, int tcnt) {
+        for (int idx = threadIdx.x; idx < tcnt * SIG_VALS; idx += nthr) {
+            const int s = idx / SIG_VALS, k = idx - s * SIG_VALS;
+            double acc = 0;
+            for (int w = 0; w < nw; w++) acc += sig[(w * FF_TILE + s) * SIG_VALS + k];
+            psb[(int64_t)(tb + s) * SIG_VALS + k] = acc;
         }
-        first = false;
     };
 
-    for (int base = s_begin; base < s_end; base += FF_TILE) {
-        const int cnt = min(FF_TILE, s_end - base);
+    int prev_base = -1;
+    for (int base = lo; base < hi; base += FF_TILE) {
+        const int cnt = min(FF_TILE, hi - base);
         __syncthreads();
-        for (int idx = threadIdx.x; idx < cnt * SM; idx += nthr) {
-            const int sl = idx / SM, f = idx - sl * SM;
+        if (prev_base >= 0) combine(prev_base, FF_TILE);
+        for (int idx = threadIdx.x; idx < cnt * SRC; idx += nthr) {
+            int s = idx / SRC, f = idx - s * SRC;
             R v;
-            if (f < GEO_STRIDE) v = geo[(int64_t)GEO_STRIDE * (base + sl) + f];
-            else if (f == OBJ) v = MULTI ? (R)tobj[base + sl] : (R)0;
-            else if (f < DYN0) v = (R)tri[3 * (base + sl) + (f - VID)];
-            else {
-                const int r = (f - DYN0) / DYN_STRIDE, c = f - DYN0 - r * DYN_STRIDE;
-                v = dyn[((int64_t)r * T + base + sl) * DYN_STRIDE + c];
-            }
+            if (f < GEO_STRIDE) v = geo[(int64_t)GEO_STRIDE * (base + s) + f];
+            else if (f < GEO_STRIDE + DYN_STRIDE)
+                v = dyn[(int64_t)DYN_STRIDE * (base + s) + (f - GEO_STRIDE)];
+            else if (f == GEO_STRIDE + DYN_STRIDE) v = MULTI ? (R)tobj[base + s] : (R)0;
+            else v = (R)tri[3 * (base + s) + (f - GEO_STRIDE - DYN_STRIDE - 1)];
             tile[idx] = v;
         }
         __syncthreads();
-        for (int sl = 0; sl < cnt; sl++) {
-            const R *src = &tile[sl * SM];
-            {
-                const R *sv = src + VID;
-                const bool adj = sv[0] == tv0 || sv[0] == tv1 || sv[0] == tv2 ||
-                                 sv[1] == tv0 || sv[1] == tv1 || sv[1] == tv2 ||
-                                 sv[2] == tv0 || sv[2] == tv1 || sv[2] == tv2;
-                if (adj) continue;   // includes sigma == tau: near field
-            }
-            const R nsx = src[18], nsy = src[19], nsz = src[20], cs = src[21];
-            const R m1 = MULTI ? (src[OBJ] == ot ? (R)1 : (R)0) : (R)1;
-            const Int<R> c1 = interior<MULTI>(cf, itab, src[OBJ]);
-            const R nn = ntx * nsx + nty * nsy + ntz * nsz;
-            const R gnr = cf.n0r * nn, gni = cf.n0i * nn;
-            R dnx[6], dny[6];
-            for (int j = 0; j < 6; j++)
-                dnx[j] = ct - (src[3 * j] * ntx + src[3 * j + 1] * nty + src[3 * j + 2] * ntz);
-            for (int i = 0; i < 6; i++)
-                dny[i] = cs - (px[i] * nsx + py[i] * nsy + pz[i] * nsz);
-            R gwr = 0, gwi = 0;
-#pragma unroll
-            for (int i = 0; i < 6; i++) {
-                R qr[NR], qi[NR], nr[NR], ni[NR];
-                for (int r = 0; r < NR; r++) qr[r] = qi[r] = nr[r] = ni[r] = 0;
-#pragma unroll
+        for (int s = 0; s < cnt; s++) {
+            const R *src = &tile[s * SRC];
+            const R *sv = src + GEO_STRIDE + DYN_STRIDE + 1;
+            const bool adj = sv[0] == tv0 || sv[0] == tv1 || sv[0] == tv2 || sv[1] == tv0 ||
+                             sv[1] == tv1 || sv[1] == tv2 || sv[2] == tv0 || sv[2] == tv1 ||
+                             sv[2] == tv2;
+            // rows of sigma contributed by this thread: 12 rows, 6 curl sums
+            R o[SIG_VALS];
+            for (int k = 0; k < SIG_VALS; k++) o[k] = 0;
+            if (active && tau < base + s && !adj) {
+                const R nsx = src[18], nsy = src[19], nsz = src[20], cs = src[21];
+                const Int<R> c1 = interior<MULTI>(cf, itab, src[GEO_STRIDE + DYN_STRIDE]);
+                const R m1 = MULTI ? (src[GEO_STRIDE + DYN_STRIDE] == ot ? (R)1 : (R)0) : (R)1;
+                const R nn = ntx * nsx + nty * nsy + ntz * nsz;
+                const R gnr = cf.n0r * nn, gni = cf.n0i * nn;
+                R dny[6];   // (y - x_i).n_sigma
+                for (int i = 0; i < 6; i++)
+                    dny[i] = cs - (px[i] * nsx + py[i] * nsy + pz[i] * nsz);
+                R gwr = 0, gwi = 0;
+#pragma unroll 1
                 for (int j = 0; j < 6; j++) {
-                    const R dx = src[3 * j] - px[i];
-                    const R dy = src[3 * j + 1] - py[i];
-                    const R dz = src[3 * j + 2] - pz[i];
-                    const R r2 = dx * dx + dy * dy + dz * dz;
-                    const R ri = MT::rsq(r2);
-                    const R rr = r2 * ri;
-                    R E0r, E0i, E1r, E1i;
-                    if constexpr (FRM) {
-                        MT::sincos_tab(rr * cf.krev0, E0i, E0r, etab);
-                        MT::sincos_tab(rr * c1.krev1, E1i, E1r, etab);
-                    } else {
-                        MT::template sincos_rev<false>(rr * cf.krev0, E0i, E0r);
-                        MT::template sincos_rev<false>(rr * c1.krev1, E1i, E1r);
-                    }
-                    if (CK0) {
-                        const R d0 = MT::exp2(rr * cf.kdec0);
-                        E0r *= d0;
-                        E0i *= d0;
-                    }
-                    if (CK1 || MULTI) {
-                        R d1 = m1;
-                        if (CK1) d1 *= MT::exp2(rr * c1.kdec1);
-                        E1r *= d1;
-                        E1i *= d1;
-                    }
-                    const R G0r = E0r * ri, G0i = E0i * ri;
-                    const R G1r = E1r * ri, G1i = E1i * ri;
-                    R Fr = fmac(c1.ns1, G1r, -G0r), Fi = fmac(c1.ns1, G1i, -G0i);
-                    Fr = fmac(-cf.k0r, E0i, Fr);
-                    Fi = fmac(cf.k0r, E0r, Fi);
-                    Fr = fmac(-c1.k1r, E1i, Fr);
-                    Fi = fmac(c1.k1r, E1r, Fi);
-                    if (CK0) {
-                        Fr = fmac(-cf.k0i, E0r, Fr);
-                        Fi = fmac(-cf.k0i, E0i, Fi);
-                    }
-                    if (CK1) {
-                        Fr = fmac(-c1.k1i, E1r, Fr);
-                        Fi = fmac(-c1.k1i, E1i, Fi);
-                    }
-                    const R ri2 = ri * ri;
-                    Fr *= ri2;
-                    Fi *= ri2;
-                    const R GVr = fmac(c1.rho, G1r, G0r), GVi = fmac(c1.rho, G1i, G0i);
-                    const R GWr = fmac(c1.irho, G1r, G0r), GWi = fmac(c1.irho, G1i, G0i);
-                    R GNr = fmac(c1.n10r, G1r, G0r), GNi = fmac(c1.n10r, G1i, G0i);
-                    if (CK0 || CK1) {
-                        GNr = fmac(-c1.n10i, G1i, GNr);
-                        GNi = fmac(c1.n10i, G1r, GNi);
-                    }
-                    const R Fxr = Fr * dnx[j], Fxi = Fi * dnx[j];
+                    const int ju = __builtin_amdgcn_readfirstlane(j);
+                    const R yx = src[3 * j], yy = src[3 * j + 1], yz = src[3 * j + 2];
+                    const R spr = src[GEO_STRIDE + 2 * j], spi = src[GEO_STRIDE + 2 * j + 1];
+                    const R sfr = src[GEO_STRIDE + 12 + 2 * j], sfi = src[GEO_STRIDE + 12 + 2 * j + 1];
+                    // dnx_j = (x - y_j).n_tau; tau-side weights dnx_j s_psi(y_j) and
+                    // -k_0^2 (n_x.n_y) s_phi(y_j)
+                    const R dnx = ct - (yx * ntx + yy * nty + yz * ntz);
+                    const R spxr = dnx * spr, spxi = dnx * spi;
+                    const R gsfr = -(gnr * sfr - gni * sfi), gsfi = -(gnr * sfi + gni * sfr);
+                    // sigma-side sums over i at y_j
+                    R u1r = 0, u1i = 0, qr = 0, qi = 0, u2r = 0, u2i = 0, nr = 0, ni = 0;
+                    R wr[2] = {0, 0}, wi[2] = {0, 0};   // sums of G_W per orbit
 #pragma unroll
-                    for (int r = 0; r < NR; r++) {
-                        const R *d = src + DYN0 + r * DYN_STRIDE;
-                        const R spr = d[2 * j], spi = d[2 * j + 1];
-                        const R sfr = d[12 + 2 * j], sfi = d[12 + 2 * j + 1];
-                        R t1r = a1r[r][i], t1i = a1i[r][i], t2r = a2r[r][i], t2i = a2i[r][i];
+                    for (int i = 0; i < 6; i++) {
+                        const R dx = yx - px[i], dy = yy - py[i], dz = yz - pz[i];
+                        const R r2 = dx * dx + dy * dy + dz * dz;
+                        const R ri = rsqrt64(r2);
+                        const R r = r2 * ri;
+                        R E0r, E0i, E1r, E1i;
+                        sincos_256(r * cf.krev0, E0i, E0r, etab);
+                        sincos_256(r * c1.krev1, E1i, E1r, etab);
+                        if (CK0) {
+                            const R d0 = decay64(r * cf.kdec0, xtab);
+                            E0r *= d0;
+                            E0i *= d0;
+                        }
+                        if (CK1 || MULTI) {
+                            R d1 = m1;
+                            if (CK1) d1 *= decay64(r * c1.kdec1, xtab);
+                            E1r *= d1;
+                            E1i *= d1;
+                        }
+                        const R G0r = E0r * ri, G0i = E0i * ri, G1r = E1r * ri, G1i = E1i * ri;
+                        R Fr = fmac(c1.ns1, G1r, -G0r), Fi = fmac(c1.ns1, G1i, -G0i);
+                        Fr = fmac(-cf.k0r, E0i, Fr);
+                        Fi = fmac(cf.k0r, E0r, Fi);
+                        Fr = fmac(-c1.k1r, E1i, Fr);
+                        Fi = fmac(c1.k1r, E1r, Fi);
+                        if (CK0) {
+                            Fr = fmac(-cf.k0i, E0r, Fr);
+                            Fi = fmac(-cf.k0i, E0i, Fi);
+                        }
+                        if (CK1) {
+                            Fr = fmac(-c1.k1i, E1r, Fr);
+                            Fi = fmac(-c1.k1i, E1i, Fi);
+                        }
+                        const R ri2 = ri * ri;
+                        Fr *= ri2;
+                        Fi *= ri2;
+                        const R GVr = fmac(c1.rho, G1r, G0r), GVi = fmac(c1.rho, G1i, G0i);
+                        R GNr = fmac(c1.n10r, G1r, G0r), GNi = fmac(c1.n10r, G1i, G0i);
+                        if (CK0 || CK1) {
+                            GNr = fmac(-c1.n10i, G1i, GNr);
+                            GNi = fmac(c1.n10i, G1r, GNi);
+                        }
+                        wr[i / 3] += fmac(c1.irho, G1r, G0r);
+                        wi[i / 3] += fmac(c1.irho, G1i, G0i);
+                        const R Kr = Fr * dny[i], Ki = Fi * dny[i];
+                        // tau at x_i: G_V s_psi(y_j) - K s_phi(y_j);
+                        //             F spx_j + G_N gsf_j
+                        R t1r = a1r[i], t1i = a1i[i], t2r = a2r[i], t2i = a2i[i];
                         t1r = fmac(GVr, spr, t1r);
                         t1r = fmac(-GVi, spi, t1r);
                         t1i = fmac(GVr, spi, t1i);
                         t1i = fmac(GVi, spr, t1i);
-                        qr[r] = fmac(Fr, sfr, qr[r]);
-                        qr[r] = fmac(-Fi, sfi, qr[r]);
-                        qi[r] = fmac(Fr, sfi, qi[r]);
-                        qi[r] = fmac(Fi, sfr, qi[r]);
-                        t2r = fmac(Fxr, spr, t2r);
-                        t2r = fmac(-Fxi, spi, t2r);
-                        t2i = fmac(Fxr, spi, t2i);
-                        t2i = fmac(Fxi, spr, t2i);
-                        nr[r] = fmac(GNr, sfr, nr[r]);
-                        nr[r] = fmac(-GNi, sfi, nr[r]);
-                        ni[r] = fmac(GNr, sfi, ni[r]);
-                        ni[r] = fmac(GNi, sfr, ni[r]);
-                        a1r[r][i] = t1r;
-                        a1i[r][i] = t1i;
-                        a2r[r][i] = t2r;
-                        a2i[r][i] = t2i;
+                        t1r = fmac(-Kr, sfr, t1r);
+                        t1r = fmac(Ki, sfi, t1r);
+                        t1i = fmac(-Kr, sfi, t1i);
+                        t1i = fmac(-Ki, sfr, t1i);
+                        t2r = fmac(Fr, spxr, t2r);
+                        t2r = fmac(-Fi, spxi, t2r);
+                        t2i = fmac(Fr, spxi, t2i);
+                        t2i = fmac(Fi, spxr, t2i);
+                        t2r = fmac(GNr, gsfr, t2r);
+                        t2r = fmac(-GNi, gsfi, t2r);
+                        t2i = fmac(GNr, gsfi, t2i);
+                        t2i = fmac(GNi, gsfr, t2i);
+                        a1r[i] = t1r;
+                        a1i[i] = t1i;
+                        a2r[i] = t2r;
+                        a2i[i] = t2i;
+                        // sigma at y_j: sums over i of G_V s_psi(x_i), F s_phi(x_i),
+                        // K s_psi(x_i) and G_N s_phi(x_i)
+                        u1r = fmac(GVr, tspr[i], u1r);
+                        u1r = fmac(-GVi, tspi[i], u1r);
+                        u1i = fmac(GVr, tspi[i], u1i);
+                        u1i = fmac(GVi, tspr[i], u1i);
+                        qr = fmac(Fr, tsfr[i], qr);
+                        qr = fmac(-Fi, tsfi[i], qr);
+                        qi = fmac(Fr, tsfi[i], qi);
+                        qi = fmac(Fi, tsfr[i], qi);
+                        u2r = fmac(Kr, tspr[i], u2r);
+                        u2r = fmac(-Ki, tspi[i], u2r);
+                        u2i = fmac(Kr, tspi[i], u2i);
+                        u2i = fmac(Ki, tspr[i], u2i);
+                        nr = fmac(GNr, tsfr[i], nr);
+                        nr = fmac(-GNi, tsfi[i], nr);
+                        ni = fmac(GNr, tsfi[i], ni);
+                        ni = fmac(GNi, tsfr[i], ni);
+                        // (two points in flight: more only spills, 1-2 % slower)
+                        if (i == 1 || i == 3) __builtin_amdgcn_sched_barrier(0);
                     }
-                    const R ww = (R)(qw(i) * qw(j));
-                    gwr = fmac(ww, GWr, gwr);
-                    gwi = fmac(ww, GWi, gwi);
-                }
+                    const R wj = kQW64[ju];
+                    gwr = fmac(wj, fmac((R)DUN_W1, wr[0], (R)DUN_W2 * wr[1]), gwr);
+                    gwi = fmac(wj, fmac((R)DUN_W1, wi[0], (R)DUN_W2 * wi[1]), gwi);
+                    // row 1 = u1 - dnx_j q; row 2 = u2 - k_0^2 (n.n) n; contracted with
+                    // w_j phi_a(y_j)
+                    const R r1r = fmac(-dnx, qr, u1r), r1i = fmac(-dnx, qi, u1i);
+                    R r2r = fmac(-gnr, nr, u2r), r2i = fmac(-gnr, ni, u2i);
+                    r2r = fmac(gni, ni, r2r);
+                    r2i = fmac(-gni, nr, r2i);
 #pragma unroll
-                for (int r = 0; r < NR; r++) {
-                    a1r[r][i] = fmac(-dny[i], qr[r], a1r[r][i]);
-                    a1i[r][i] = fmac(-dny[i], qi[r], a1i[r][i]);
-                    R t2r = a2r[r][i], t2i = a2i[r][i];
-                    t2r = fmac(-gnr, nr[r], t2r);
-                    t2r = fmac(gni, ni[r], t2r);
-                    t2i = fmac(-gnr, ni[r], t2i);
-                    t2i = fmac(-gni, nr[r], t2i);
-                    a2r[r][i] = t2r;
-                    a2i[r][i] = t2i;
+                    for (int a = 0; a < 3; a++) {
+                        const R wb = kQWB64[3 * ju + a];
+                        o[2 * a] = fmac(wb, r1r, o[2 * a]);
+                        o[2 * a + 1] = fmac(wb, r1i, o[2 * a + 1]);
+                        o[6 + 2 * a] = fmac(wb, r2r, o[6 + 2 * a]);
+                        o[6 + 2 * a + 1] = fmac(wb, r2i, o[6 + 2 * a + 1]);
+                    }
+                }
+                // curl terms: A_tau += g_W C_sigma, A_sigma += g_W C_tau
+                for (int k = 0; k < 3; k++) {
+                    const R scr = src[GEO_STRIDE + 24 + 2 * k], sci = src[GEO_STRIDE + 24 + 2 * k + 1];
+                    R *A = curl + 2 * k * nthr + threadIdx.x;
+                    A[0] += gwr * scr - gwi * sci;
+                    A[nthr] += gwr * sci + gwi * scr;
+                    const R tr = own[2 * k * nthr + threadIdx.x], ti = own[(2 * k + 1) * nthr + threadIdx.x];
+                    o[ROW_STRIDE + 2 * k] = gwr * tr - gwi * ti;
+                    o[ROW_STRIDE + 2 * k + 1] = gwr * ti + gwi * tr;
                 }
             }
+            // sums over the wave's lanes: after the two swaps a row of 16 lanes holds
+            // values k + {0, 5, 9, 14}[row] (k < 4) and 4 or 13 (k = 4)
+            R w9[9], w5[5];
 #pragma unroll
-            for (int r = 0; r < NR; r++) {
-                const R *d = src + DYN0 + r * DYN_STRIDE;
-                for (int c = 0; c < 3; c++) {
-                    const R scr = d[24 + 2 * c], sci = d[24 + 2 * c + 1];
-                    Ar[r][c] += gwr * scr - gwi * sci;
-                    Ai[r][c] += gwr * sci + gwi * scr;
-                }
+            for (int k = 0; k < 9; k++) w9[k] = swap_add32(o[k], o[k + 9]);
+#pragma unroll
+            for (int k = 0; k < 5; k++) w5[k] = swap_add16(w9[k], w9[k < 4 ? k + 5 : 4]);
+#pragma unroll
+            for (int k = 0; k < 5; k++) w5[k] = row_sum64(w5[k]);
+            if ((threadIdx.x & 15) == 0) {
+                const int row = (threadIdx.x >> 4) & 3;
+                R *out = sig + (wave * FF_TILE + s) * SIG_VALS + 9 * (row >> 1);
+#pragma unroll
+                for (int k = 0; k < 4; k++) out[k + 5 * (row & 1)] = w5[k];
+                if (!(row & 1)) out[4] = w5[4];
             }
         }
-        flush();
+        prev_base = base;
     }
-    if (first) flush();   // empty split: zero partials
+    __syncthreads();
+    if (prev_base >= 0) combine(prev_base, hi - prev_base);
+    if (!active) return;
+    double *out = ptau + ((int64_t)canon * nthr + threadIdx.x) * SIG_VALS;
+    for (int a = 0; a < 3; a++) {
+        double r1r = 0, r1i = 0, r2r = 0, r2i = 0;
+        for (int i = 0; i < 6; i++) {
+            const double wb = qw(i) * qb(i, a);
+            r1r += wb * a1r[i];
+            r1i += wb * a1i[i];
+            r2r += wb * a2r[i];
+            r2i += wb * a2i[i];
+        }
+        out[2 * a] = r1r;
+        out[2 * a + 1] = r1i;
+        out[6 + 2 * a] = r2r;
+        out[6 + 2 * a + 1] = r2i;
+    }
+    for (int k = 0; k < 6; k++) out[ROW_STRIDE + k] = curl[k * nthr + threadIdx.x];
 }
 
 // --------------------------------------------------------- split reduction
@@ -1110,89 +1124,107 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(
 }
 
 // ------------------------------------------- symmetric-kernel reduction
-// Rows of test triangle tau from the symmetric kernel: its own work items
-// as tau (chunk order), then its sum as sigma over the blocks b <=
-// block(tau); then the curl contraction and |tau|/(4 pi) as in the split
-// reduction.
-// sigacc[sigma] (+)= the slots of blocks [b0, b1) for sigma (block order;
-// the round of block 0 starts every sum)
+// Rows of test triangle tau from the symmetric kernel: its own work items as
+// tau (chunk order) and its slots as sigma over the blocks b <= block(tau)
+// (block order); then the curl contraction and |tau|/(4 pi) as in the split
+// reduction.  A thread per (triangle, value, one of RED_LANES shares of the
+// chunks and blocks), so that the loads of a wavefront are consecutive and no
+// sum is one serial chain: with a thread per triangle the two kernels took 28
+// and 7 us on 1 280 triangles in 32-triangle chunks (109 us in chunks of 8).
+constexpr int RED_LANES = 4;   // a power of two
+constexpr int RED_TRI = 256 / (SIG_VALS * RED_LANES);   // triangles per workgroup
+
+// This thread's share (blocks congruent to `share` modulo RED_LANES, in order) of
+// value k of triangle t over the slots of blocks [b0, b1), added to acc: the same
+// additions in the same order however the blocks are split into rounds.
+__device__ __forceinline__ double sig_share(double acc, const double *__restrict__ psig,
+                                            int64_t sig_base, int b0, int b1, int T, int blk, int t,
+                                            int k, int share) {
+    const int last = min(b1 - 1, t / blk);
+#pragma unroll 4
+    for (int bb = b0 + ((share - b0) & (RED_LANES - 1)); bb <= last; bb += RED_LANES)
+        acc += psig[(sym_sig_off(bb, T, blk) - sig_base + t - (int64_t)bb * blk) * SIG_VALS + k];
+    return acc;
+}
+
+// sigacc[share][sigma] (+)= the slots of blocks [b0, b1) (the round of block 0
+// starts every sum): after every round but the last
 __global__ __launch_bounds__(256) void sym_sig_accum_kernel(
     const double *__restrict__ psig, int64_t sig_base, int b0, int b1, int T, int blk,
     double *__restrict__ sigacc) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T || t < b0 * blk) return;
-    double acc[SIG_VALS];
-    double *o = sigacc + (int64_t)t * SIG_VALS;
-    for (int k = 0; k < SIG_VALS; k++) acc[k] = b0 == 0 ? 0.0 : o[k];
-    const int last = min(b1 - 1, t / blk);
-    for (int bb = b0; bb <= last; bb++) {
-        const double *q = psig + (sym_sig_off(bb, T, blk) - sig_base + t - (int64_t)bb * blk) * SIG_VALS;
-        for (int k = 0; k < SIG_VALS; k++) acc[k] += q[k];
-    }
-    for (int k = 0; k < SIG_VALS; k++) o[k] = acc[k];
+    const int v = threadIdx.x % (RED_TRI * SIG_VALS), share = threadIdx.x / (RED_TRI * SIG_VALS);
+    const int t = blockIdx.x * RED_TRI + v / SIG_VALS, k = v % SIG_VALS;
+    if (share >= RED_LANES || t >= T || t < b0 * blk) return;
+    double *o = sigacc + ((int64_t)share * T + t) * SIG_VALS + k;
+    *o = sig_share(b0 == 0 ? 0.0 : *o, psig, sig_base, b0, b1, T, blk, t, k, share);
 }
 
+// the last round's slots [b0, b1); sigacc: the earlier rounds' sums (b0 > 0)
 __global__ __launch_bounds__(256) void reduce_sym_kernel(
-    const double *__restrict__ ptau, const double *__restrict__ sigacc,
-    const double *__restrict__ tst, int T, int blk, int chunk_len,
+    const double *__restrict__ ptau, const double *__restrict__ psig, int64_t sig_base, int b0, int b1,
+    const double *__restrict__ sigacc, const double *__restrict__ tst, int T, int blk, int chunk_len,
     double *__restrict__ trirows) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    const int b = t / blk, l = t - b * blk;
-    int64_t first = 0;
-    for (int bb = 0; bb < b; bb++) first += (T - bb * blk + chunk_len - 1) / chunk_len;
-    const int nch = (T - b * blk + chunk_len - 1) / chunk_len;
-    double acc[SIG_VALS];
-    for (int k = 0; k < SIG_VALS; k++) acc[k] = 0;
-    for (int c = 0; c < nch; c++) {
-        const double *p = ptau + ((first + c) * blk + l) * SIG_VALS;
-        for (int k = 0; k < SIG_VALS; k++) acc[k] += p[k];
+    __shared__ double part[RED_LANES][RED_TRI * SIG_VALS];
+    const int v = threadIdx.x % (RED_TRI * SIG_VALS), share = threadIdx.x / (RED_TRI * SIG_VALS);
+    const int tl = v / SIG_VALS, k = v % SIG_VALS;
+    const int t = blockIdx.x * RED_TRI + tl;
+    const bool in = share < RED_LANES && t < T;
+    if (in) {
+        const int b = t / blk, l = t - b * blk;
+        int64_t first = 0;
+        for (int bb = 0; bb < b; bb++) first += (T - bb * blk + chunk_len - 1) / chunk_len;
+        const int nch = (T - b * blk + chunk_len - 1) / chunk_len;
+        double acc = 0;
+#pragma unroll 4
+        for (int c = share; c < nch; c += RED_LANES) acc += ptau[((first + c) * blk + l) * SIG_VALS + k];
+        const double before = b0 > 0 ? sigacc[((int64_t)share * T + t) * SIG_VALS + k] : 0.0;
+        part[share][v] = acc + sig_share(before, psig, sig_base, b0, b1, T, blk, t, k, share);
     }
-    {
-        const double *q = sigacc + (int64_t)t * SIG_VALS;
-        for (int k = 0; k < SIG_VALS; k++) acc[k] += q[k];
-    }
+    __syncthreads();
+    if (in && share == 0)
+        for (int q = 1; q < RED_LANES; q++) part[0][v] += part[q][v];
+    __syncthreads();
+    if (!in || share != 0 || k >= ROW_STRIDE) return;
+    const double *row = part[0] + tl * SIG_VALS, *A = row + ROW_STRIDE;
     const double *ts = tst + (int64_t)TST_STRIDE * t;
-    const double sc = ts[0] * 0.079577471545947667884441881686257;   // |tau|/(4 pi)
-    const double *A = acc + ROW_STRIDE;
-    for (int a = 0; a < 3; a++) {
+    double acc = row[k];
+    if (k >= 6) {   // row 2 of vertex a, re or im
+        const int a = (k - 6) >> 1, c = k & 1;
         const double *cu = ts + 1 + 3 * a;
-        acc[6 + 2 * a] += cu[0] * A[0] + cu[1] * A[2] + cu[2] * A[4];
-        acc[6 + 2 * a + 1] += cu[0] * A[1] + cu[1] * A[3] + cu[2] * A[5];
+        acc += cu[0] * A[c] + cu[1] * A[2 + c] + cu[2] * A[4 + c];
     }
-    for (int c = 0; c < ROW_STRIDE; c++) trirows[(int64_t)ROW_STRIDE * t + c] = sc * acc[c];
+    trirows[(int64_t)ROW_STRIDE * t + k] = ts[0] * 0.079577471545947667884441881686257 * acc;
 }
 
 // ------------------------------------- vertex gather + near-field CSR SpMV
+// 16 lanes per vertex
 __global__ __launch_bounds__(256) void finalize_kernel(
     const double *__restrict__ trirows, const int32_t *__restrict__ star_ptr,
     const int32_t *__restrict__ star_idx, const int32_t *__restrict__ rowptr,
     const int32_t *__restrict__ col, const double2 *__restrict__ nf, int64_t nnz,
     const double2 *__restrict__ x, int64_t N, double2 *__restrict__ y) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    double y1r = 0, y1i = 0, y2r = 0, y2i = 0;
-    for (int e = star_ptr[i]; e < star_ptr[i + 1]; e++) {
-        int ta = star_idx[e];
-        int t = ta / 3, a = ta - 3 * t;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / NEAR_LANES;
+    const int lane = threadIdx.x % NEAR_LANES;
+    if (i >= N) return;   // (whole groups)
+    double2 y1 = make_double2(0, 0), y2 = make_double2(0, 0);
+    for (int e = star_ptr[i] + lane; e < star_ptr[i + 1]; e += NEAR_LANES) {
+        const int ta = star_idx[e];
+        const int t = ta / 3, a = ta - 3 * t;
         const double *r = trirows + (int64_t)ROW_STRIDE * t;
-        y1r += r[2 * a];
-        y1i += r[2 * a + 1];
-        y2r += r[6 + 2 * a];
-        y2i += r[6 + 2 * a + 1];
+        y1.x += r[2 * a];
+        y1.y += r[2 * a + 1];
+        y2.x += r[6 + 2 * a];
+        y2.y += r[6 + 2 * a + 1];
     }
-    const double2 *C11 = nf, *C12 = nf + nnz, *C21 = nf + 2 * nnz, *C22 = nf + 3 * nnz;
-    for (int e = rowptr[i]; e < rowptr[i + 1]; e++) {
-        int j = col[e];
-        double2 p = x[j], f = x[N + j];
-        double2 a = C11[e], b = C12[e], c = C21[e], d = C22[e];
-        y1r += a.x * p.x - a.y * p.y + b.x * f.x - b.y * f.y;
-        y1i += a.x * p.y + a.y * p.x + b.x * f.y + b.y * f.x;
-        y2r += c.x * p.x - c.y * p.y + d.x * f.x - d.y * f.y;
-        y2i += c.x * p.y + c.y * p.x + d.x * f.y + d.y * f.x;
+    near_row(lane, i, rowptr, col, nf, nnz, x, N, y1, y2);
+    y1.x = near_sum(y1.x);
+    y1.y = near_sum(y1.y);
+    y2.x = near_sum(y2.x);
+    y2.y = near_sum(y2.y);
+    if (lane == 0) {
+        y[i] = y1;
+        y[N + i] = y2;
     }
-    y[i] = make_double2(y1r, y1i);
-    y[N + i] = make_double2(y2r, y2i);
 }
 
 // s1 = +1: PMCHWT (A_0 + A^_1); s1 = -1: the interior terms of the Mueller
@@ -1203,7 +1235,7 @@ template <class R> Int<R> make_int(double2 k0, double2 k1, double rho, int s1) {
     Int<R> c;
     const double inv2pi = 0.15915494309189533576888376337251;
     const double log2e = 1.4426950408889634073599246810019;
-    c.krev1 = (R)(k1.x * inv2pi);
+    c.krev1 = (R)(k1.x * inv2pi * phase_unit<R>());
     c.k1r = (R)k1.x;
     c.k1i = (R)k1.y;
     c.kdec1 = (R)(-k1.y * log2e);
@@ -1234,7 +1266,7 @@ template <class R> Coef<R> make_coef(double2 k0, const NearOperator &nf) {
     Coef<R> c;
     const double inv2pi = 0.15915494309189533576888376337251;
     const double log2e = 1.4426950408889634073599246810019;
-    c.krev0 = (R)(k0.x * inv2pi);
+    c.krev0 = (R)(k0.x * inv2pi * phase_unit<R>());
     c.k0r = (R)k0.x;
     c.k0i = (R)k0.y;
     c.kdec0 = (R)(-k0.y * log2e);
@@ -1269,6 +1301,13 @@ template <class R> const Int<R> *interior_table(const bem_mesh *m, const NearOpe
 // dynamic LDS of the single-vector kernel: FP32 per-thread FP64 sums
 template <class R> size_t far_smem(int blk) {
     return std::is_same<R, float>::value ? (size_t)FF_ROWS * blk * sizeof(double) : 0;
+}
+
+// dynamic LDS of the symmetric kernels
+template <class R> size_t sym_smem(int blk) {
+    return std::is_same<R, float>::value
+               ? far_smem<R>(blk)
+               : (size_t)(12 * blk + blk / 64 * FF_TILE * SIG_VALS) * sizeof(double);
 }
 
 template <class R, bool CK0, bool CK1, bool MULTI, bool FR>
@@ -1315,41 +1354,6 @@ template <class R, bool FR> const void *far_kernel(int code) {
     case 5: return (const void *)farfield_kernel<R, true, false, true, FR>;
     case 6: return (const void *)farfield_kernel<R, true, true, false, FR>;
     default: return (const void *)farfield_kernel<R, true, true, true, FR>;
-    }
-}
-
-template <class R, int NR> const void *multi_kernel(int code) {
-    switch (code) {
-    case 0: return (const void *)farfield_multi_kernel<R, false, false, false, NR>;
-    case 1: return (const void *)farfield_multi_kernel<R, false, false, true, NR>;
-    case 2: return (const void *)farfield_multi_kernel<R, false, true, false, NR>;
-    case 3: return (const void *)farfield_multi_kernel<R, false, true, true, NR>;
-    case 4: return (const void *)farfield_multi_kernel<R, true, false, false, NR>;
-    case 5: return (const void *)farfield_multi_kernel<R, true, false, true, NR>;
-    case 6: return (const void *)farfield_multi_kernel<R, true, true, false, NR>;
-    default: return (const void *)farfield_multi_kernel<R, true, true, true, NR>;
-    }
-}
-
-template <class R, int NR>
-void launch_multi(int code, dim3 grid, int blk, hipStream_t s, const R *geo, const R *dyn,
-                  const int32_t *tobj, const int32_t *tri, int T, int split_len, Coef<R> cf,
-                  const Int<R> *itab, double *partial) {
-    switch (code) {
-#define BEM_CASE(c, a, b, m)                                                                     \
-    case c:                                                                                      \
-        hipLaunchKernelGGL((farfield_multi_kernel<R, a, b, m, NR>), grid, dim3(blk), 0, s,      \
-                           geo, dyn, tobj, tri, T, split_len, cf, itab, partial);                \
-        break;
-        BEM_CASE(0, false, false, false)
-        BEM_CASE(1, false, false, true)
-        BEM_CASE(2, false, true, false)
-        BEM_CASE(3, false, true, true)
-        BEM_CASE(4, true, false, false)
-        BEM_CASE(5, true, false, true)
-        BEM_CASE(6, true, true, false)
-        BEM_CASE(7, true, true, true)
-#undef BEM_CASE
     }
 }
 
@@ -1426,53 +1430,47 @@ FarPlan far_plan(const bem_mesh *m, int precision, double2 k0, double2 k1, int b
 
 int valid_block(int b) { return b == 64 || b == 128 || b == 256 ? b : 256; }
 
-// Symmetric kernel variant for the runtime flags (code = 4 ck0 + 2 ck1 + multi).
-template <bool FR> const void *sym_kernel(int code) {
-    switch (code) {
-    case 0: return (const void *)farfield_sym_kernel<float, false, false, false, FR>;
-    case 1: return (const void *)farfield_sym_kernel<float, false, false, true, FR>;
-    case 2: return (const void *)farfield_sym_kernel<float, false, true, false, FR>;
-    case 3: return (const void *)farfield_sym_kernel<float, false, true, true, FR>;
-    case 4: return (const void *)farfield_sym_kernel<float, true, false, false, FR>;
-    case 5: return (const void *)farfield_sym_kernel<float, true, false, true, FR>;
-    case 6: return (const void *)farfield_sym_kernel<float, true, true, false, FR>;
-    default: return (const void *)farfield_sym_kernel<float, true, true, true, FR>;
-    }
+// Symmetric kernel variant for the runtime flags (code = 4 ck0 + 2 ck1 + multi;
+// fr: FP32 phases reduced).
+template <class R>
+using SymFn = void (*)(const R *, const R *, const int32_t *, const int32_t *, int, const int32_t *,
+                       int, Coef<R>, const Int<R> *, double *, double *, int64_t);
+template <class R, bool A, bool B, bool M> SymFn<R> sym_variant(bool fr) {
+    if constexpr (std::is_same<R, double>::value) return farfield_sym64_kernel<A, B, M>;
+    else return fr ? farfield_sym_kernel<float, A, B, M, true> : farfield_sym_kernel<float, A, B, M, false>;
 }
-
-template <bool FR>
-void launch_sym(int code, int n_items, int blk, hipStream_t s, const float *geo, const float *dyn,
-                const int32_t *tobj, const int32_t *tri, int T, const int32_t *items, int chunk,
-                Coef<float> cf, const Int<float> *itab, double *ptau, double *psig,
-                int64_t sig_base) {
+template <class R> SymFn<R> sym_kernel(int code, bool fr) {
     switch (code) {
-#define BEM_CASE(c, a, b, m)                                                                     \
-    case c:                                                                                      \
-        hipLaunchKernelGGL((farfield_sym_kernel<float, a, b, m, FR>), dim3(n_items), dim3(blk),  \
-                           far_smem<float>(blk), s, geo, dyn, tobj, tri, T, items, chunk, cf,    \
-                           itab, ptau, psig, sig_base);                                          \
-        break;
-        BEM_CASE(0, false, false, false)
-        BEM_CASE(1, false, false, true)
-        BEM_CASE(2, false, true, false)
-        BEM_CASE(3, false, true, true)
-        BEM_CASE(4, true, false, false)
-        BEM_CASE(5, true, false, true)
-        BEM_CASE(6, true, true, false)
-        BEM_CASE(7, true, true, true)
-#undef BEM_CASE
+    case 0: return sym_variant<R, false, false, false>(fr);
+    case 1: return sym_variant<R, false, false, true>(fr);
+    case 2: return sym_variant<R, false, true, false>(fr);
+    case 3: return sym_variant<R, false, true, true>(fr);
+    case 4: return sym_variant<R, true, false, false>(fr);
+    case 5: return sym_variant<R, true, false, true>(fr);
+    case 6: return sym_variant<R, true, true, false>(fr);
+    default: return sym_variant<R, true, true, true>(fr);
     }
 }
 
 // Work items of the symmetric kernel.  Block b (test triangles
 // [b blk, b blk + blk)) meets the trial triangles [b blk, T) in chunks of
-// `chunk`; the chunk length is the multiple of the tile that minimises the
-// makespan of a greedy list schedule of the items (longest first) on the
-// resident workgroup slots, among lengths giving 1.5 to 8 items per slot.  Launch order: full chunks, then the shorter
+// `chunk`.  Launch order: full chunks, then the shorter
 // last chunks by decreasing length; storage order of the tau rows: b-major.
 // Rounds: consecutive block ranges [b0, b1) whose sigma slots take at most
 // "farfield.sym_round_mib" (one launch each), their items at [item0, item0 +
 // nitems).
+//
+// Chunk length: an item costs about as much as four more trial triangles
+// (loading its test triangles, storing their rows), and the launch ends with
+// half a chunk of idle slots, so with w trial triangles of work per resident
+// workgroup the time is about w (1 + 4 / L) + L, least at L = 2 sqrt(w).
+// Measured optima (two workgroups a CU): 4 at 720 triangles, 8 at 1 280, 12 to
+// 24 at 2 880, 24 at 5 120 and 8 000, 64 at 12 500, 64 to 96 at 20 480, flat
+// from 64 to 300 at 40 500.  A list-schedule model, which took the slots as
+// independent, chose chunks two to eight times longer: 0.21 -> 0.09 ms at 1 280
+// triangles, 14.7 -> 14.1 at 20 480, 61.6 -> 54.6 at 40 500.
+constexpr int SYM_CHUNK_MAX = 96;
+constexpr int64_t SYM_ITEMS_MAX = 16384;   // bounds the tau rows (0.6 GB at 256)
 struct SymRound {
     int b0, b1, item0, nitems;
     int64_t sig_base;   // sym_sig_off(b0)
@@ -1482,6 +1480,7 @@ struct SymPlan {
     std::vector<int32_t> items;   // launch order, round after round: (b, c, storage index)
     std::vector<SymRound> rounds;
     int64_t tau_doubles = 0, sig_doubles = 0;   // sig_doubles: the largest round
+    int64_t acc_doubles = 0;   // sums over the earlier rounds
 };
 
 const SymPlan &sym_plan(int T, int blk, int slots) {
@@ -1504,57 +1503,22 @@ const SymPlan &sym_plan(int T, int blk, int slots) {
         b0 = b1;
     }
     const int64_t nr = (int64_t)rounds.size();
-    const double fixed = 2.0;
-    int best_L = T;
-    double best_cost = 1e300;
-    std::vector<int> lens;
-    // At about one item per slot the launch measured 8 % slower than the
-    // schedule predicts (icosphere L5: 17.2 ms at 800 items, 15.9 ms at 1562
-    // on 768 slots), so lengths giving at least 1.5 items per slot and round
-    // are preferred where the mesh has enough pairs; each round is a launch
-    // of its own, so the cost is the sum of the rounds' makespans.
-    int64_t max_items = 0;
-    for (int b = 0; b < nblk; b++) max_items += (T - b * blk + FF_TILE - 1) / FF_TILE;
-    const int64_t min_items = std::min<int64_t>(3 * (int64_t)slots / 2 * nr, max_items);
-    for (int L = FF_TILE; L < T + FF_TILE; L += FF_TILE) {
-        int64_t n_items = 0;
-        for (int b = 0; b < nblk; b++) n_items += (T - b * blk + L - 1) / L;
-        // beyond a few rounds finer chunks only add partial-buffer traffic
-        if (n_items > std::min<int64_t>(50000, 8 * (int64_t)slots * nr)) continue;
-        if (n_items < min_items) break;   // fewer items for every longer chunk
-        double cost = 0;
-        for (const auto &r : rounds) {
-            lens.clear();
-            for (int b = r.first; b < r.second; b++)
-                for (int lo = b * blk; lo < T; lo += L) lens.push_back(std::min(L, T - lo));
-            std::sort(lens.begin(), lens.end(), std::greater<int>());
-            std::priority_queue<double, std::vector<double>, std::greater<double>> q;
-            for (int i = 0; i < slots; i++) q.push(0.0);
-            double makespan = 0;
-            for (int len : lens) {
-                const double t = q.top() + len + fixed;
-                q.pop();
-                q.push(t);
-                makespan = std::max(makespan, t);
-            }
-            cost += makespan;
-        }
-        if (cost < best_cost * (1.0 - 1e-9)) {
-            best_cost = cost;
-            best_L = L;
-        }
-        if (L >= 8192) break;
-    }
+    const double work = 0.5 * T * ((double)T / blk + 1.0);   // trial triangles of all blocks
+    double len = 2.0 * std::sqrt(work / slots);   // (whatever the rounds: the sums do not depend on them)
+    len = std::max(std::min(len, (double)SYM_CHUNK_MAX), work / SYM_ITEMS_MAX);
+    // whole tiles beyond one, multiples of 4 below
+    const int unit = len > FF_TILE ? FF_TILE : 4;
+    const int chunk = std::max(unit, unit * (int)std::lround(len / unit));
     SymPlan p;
     p.blk = blk;
-    p.chunk = best_L;
+    p.chunk = chunk;
     p.nblk = nblk;
     std::vector<std::array<int32_t, 4>> all;   // (len, b, c, canon), block-major
     int32_t canon = 0;
     for (int b = 0; b < nblk; b++) {
         int c = 0;
-        for (int lo = b * blk; lo < T; lo += best_L, c++)
-            all.push_back({std::min(best_L, T - lo), b, c, canon++});
+        for (int lo = b * blk; lo < T; lo += chunk, c++)
+            all.push_back({std::min(chunk, T - lo), b, c, canon++});
     }
     size_t e0 = 0;
     for (const auto &r : rounds) {
@@ -1578,20 +1542,21 @@ const SymPlan &sym_plan(int T, int blk, int slots) {
         e0 = e1;
     }
     p.tau_doubles = (int64_t)canon * blk * SIG_VALS;
+    if (nr > 1) p.acc_doubles = (int64_t)RED_LANES * T * SIG_VALS;
     return cache.emplace(std::make_tuple(T, blk, slots, cap_mib), std::move(p)).first->second;
 }
 
-const SymPlan &sym_plan_for(const bem_mesh *m, const FarPlan &fp) {
-    const void *k = fp.fr ? sym_kernel<true>(fp.code) : sym_kernel<false>(fp.code);
-    return sym_plan((int)m->T, fp.blk, far_slots(k, fp.blk, far_smem<float>(fp.blk)));
+template <class R> const SymPlan &sym_plan_for(const bem_mesh *m, const FarPlan &fp) {
+    return sym_plan((int)m->T, fp.blk, far_slots((const void *)sym_kernel<R>(fp.code, fp.fr), fp.blk,
+                                                 sym_smem<R>(fp.blk)));
 }
 
 
 }   // namespace
 
 // Vectors from which the batch kernel is used: its time hardly depends on the
-// number of vectors.  6 252 vertices, ms: FP32 12.5 for 2 to 8 vectors, 6.1 each
-// alone, 11.5 for two sharing a launch; FP64 27.9, 16.8 and 24.3.
+// number of vectors.  6 252 vertices, ms for 2 to 8 vectors: FP32 12.5 against
+// 5.4 a vector alone, FP64 25 against 10.9.
 constexpr int FF_BATCH_MIN = 3;
 
 // Upper bound over every block size and the batch kernel's launches, so that
@@ -1600,49 +1565,49 @@ int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, dou
     const int64_t T = m->T;
     const bool f32 = precision == BEM_FP32;
     const int64_t rb = f32 ? 4 : 8;
-    const int64_t dyn = (R < 2 ? 1 : 2) * T * DYN_STRIDE * rb;
+    const int64_t dyn = T * DYN_STRIDE * rb;
     int64_t part = 0;
     for (int blk : {64, 128, 256}) {
         const FarPlan p = far_plan(m, precision, k0, k1, blk);
         part = std::max(part, (int64_t)p.nsplit * T * (ROW_STRIDE + 6) * 8);
-        if (f32) {
-            const SymPlan &sp = sym_plan_for(m, p);
-            part = std::max(part, (sp.tau_doubles + sp.sig_doubles + T * SIG_VALS) * 8 +
+        {
+            const SymPlan &sp = f32 ? sym_plan_for<float>(m, p) : sym_plan_for<double>(m, p);
+            part = std::max(part, (sp.tau_doubles + sp.sig_doubles + sp.acc_doubles) * 8 +
                                       (int64_t)sp.items.size() * 4);
         }
-        if (R < 2 || (f32 && p.fr)) continue;
-        const void *k = f32 ? multi_kernel<float, 2>(p.code) : multi_kernel<double, 2>(p.code);
-        part = std::max(part, (int64_t)2 * farfield_splits((int)T, far_slots(k, blk, 0), blk) * T *
-                                  (ROW_STRIDE + 6) * 8);
     }
     if (R >= FF_BATCH_MIN) part = std::max(part, farfield_mx_bytes(m, precision, k0, k1, R));
     return dyn + part + T * ROW_STRIDE * 8;
 }
 
-void farfield_apply(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
-                    double rho, const double2 *x, double2 *y, int precision,
-                    hipStream_t s, int block) {
-    const int T = (int)m->T;
-    const FarPlan plan =
-        far_plan(m, precision, k0, nf.k1_plan, valid_block(block > 0 ? block : tune_lookup(T, 1).block));
-    const int blk = plan.blk;
-    const int nsplit = plan.nsplit;
-    const bool ck0 = k0.y != 0.0, ck1 = nf.k1_plan.y != 0.0, multi = m->nobj > 1, fr = plan.fr;
-    const int split_len = (T + nsplit - 1) / nsplit;
-    const bool sym = precision == BEM_FP32 && tuning().farfield_symmetric;
-    const size_t need = (size_t)nsplit * T * (ROW_STRIDE + 6);
-    if (!sym && m->partial.n < need) m->partial.alloc(need);
+namespace {
+
+// One vector in precision R.
+template <class R>
+void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &plan,
+               const double2 *x, double2 *y, hipStream_t s) {
+    constexpr bool F32 = std::is_same<R, float>::value;
+    const int T = (int)m->T, blk = plan.blk;
+    auto &dynb = [&]() -> auto & {
+        if constexpr (F32) return m->dyn32;
+        else return m->dyn64;
+    }();
+    const R *geo;
+    if constexpr (F32) geo = m->geo32.p;
+    else geo = m->geo64.p;
     if (m->trirows.n < (size_t)T * ROW_STRIDE) m->trirows.alloc((size_t)T * ROW_STRIDE);
-    dim3 gg((T + 255) / 256);
-    dim3 grid((T + blk - 1) / blk, nsplit);
-    if (sym) {
+    if (dynb.n < (size_t)T * DYN_STRIDE) dynb.alloc((size_t)T * DYN_STRIDE);
+    const R *dyn = dynb.p;
+    const dim3 gg((T + 255) / 256);
+    hipLaunchKernelGGL(source_gather_kernel<R>, gg, dim3(256), 0, s, m->tri_d.p, m->tst.p, x, m->N, T,
+                       dynb.p);
+    const Coef<R> cf = make_coef<R>(k0, nf);
+    const Int<R> *it = interior_table<R>(m, nf, k0);
+    const char *name = F32 ? "farfield_fp32" : "farfield_fp64";
+    if (tuning().farfield_symmetric) {
         // each separated pair once, rows of both triangles
-        if (m->dyn32.n < (size_t)T * DYN_STRIDE) m->dyn32.alloc((size_t)T * DYN_STRIDE);
-        hipLaunchKernelGGL(source_gather_kernel<float>, gg, dim3(256), 0, s, m->tri_d.p,
-                           m->tst.p, x, m->N, T, m->dyn32.p);
-        BEM_LAUNCH_CHECK();
-        const SymPlan &sp = sym_plan_for(m, plan);
-        const size_t sneed = (size_t)(sp.tau_doubles + sp.sig_doubles + (int64_t)T * SIG_VALS);
+        const SymPlan &sp = sym_plan_for<R>(m, plan);
+        const size_t sneed = (size_t)(sp.tau_doubles + sp.sig_doubles + sp.acc_doubles);
         if (m->partial.n < sneed) m->partial.alloc(sneed);
         if (m->sym_items.n < sp.items.size() || m->sym_plan_id != &sp) {
             if (m->sym_items.n < sp.items.size()) m->sym_items.alloc(sp.items.size());
@@ -1651,125 +1616,60 @@ void farfield_apply(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
             m->sym_plan_id = &sp;
         }
         double *ptau = m->partial.p, *psig = ptau + sp.tau_doubles, *sigacc = psig + sp.sig_doubles;
-        const Coef<float> cf = make_coef<float>(k0, nf);
-        const Int<float> *it = interior_table<float>(m, nf, k0);
+        const dim3 gr((T + RED_TRI - 1) / RED_TRI);
         auto accum = [&](const SymRound &rd) {
-            hipLaunchKernelGGL(sym_sig_accum_kernel, gg, dim3(256), 0, s, psig, rd.sig_base, rd.b0,
+            hipLaunchKernelGGL(sym_sig_accum_kernel, gr, dim3(256), 0, s, psig, rd.sig_base, rd.b0,
                                rd.b1, T, blk, sigacc);
-            BEM_LAUNCH_CHECK();
         };
         {
-            Timer tm("farfield_fp32", s);
+            Timer tm(name, s);
+            const SymFn<R> fn = sym_kernel<R>(plan.code, plan.fr);
             const size_t nr = sp.rounds.size();
             for (size_t r = 0; r < nr; r++) {
                 const SymRound &rd = sp.rounds[r];
-                const int32_t *items = m->sym_items.p + 3 * (int64_t)rd.item0;
-                if (!fr)
-                    launch_sym<false>(plan.code, rd.nitems, blk, s, m->geo32.p, m->dyn32.p,
-                                      m->tobj_d.p, m->tri_d.p, T, items, sp.chunk, cf, it, ptau,
-                                      psig, rd.sig_base);
-                else
-                    launch_sym<true>(plan.code, rd.nitems, blk, s, m->geo32.p, m->dyn32.p,
-                                     m->tobj_d.p, m->tri_d.p, T, items, sp.chunk, cf, it, ptau,
-                                     psig, rd.sig_base);
-                BEM_LAUNCH_CHECK();
+                hipLaunchKernelGGL(fn, dim3(rd.nitems), dim3(blk), sym_smem<R>(blk), s, geo, dyn,
+                                   m->tobj_d.p, m->tri_d.p, T, m->sym_items.p + 3 * (int64_t)rd.item0,
+                                   sp.chunk, cf, it, ptau, psig, rd.sig_base);
                 if (r + 1 < nr) accum(rd);   // the slots are reused by the next round
             }
         }
-        accum(sp.rounds.back());
-        hipLaunchKernelGGL(reduce_sym_kernel, gg, dim3(256), 0, s, ptau, sigacc, m->tst.p, T, blk,
-                           sp.chunk, m->trirows.p);
-        BEM_LAUNCH_CHECK();
-    } else if (precision == BEM_FP32) {
-        if (m->dyn32.n < (size_t)T * DYN_STRIDE) m->dyn32.alloc((size_t)T * DYN_STRIDE);
-        hipLaunchKernelGGL(source_gather_kernel<float>, gg, dim3(256), 0, s, m->tri_d.p,
-                           m->tst.p, x, m->N, T, m->dyn32.p);
-        BEM_LAUNCH_CHECK();
-        Timer tm("farfield_fp32", s);
-        if (!fr)
-            dispatch_far<float, false>(grid, blk, s, m->geo32.p, m->dyn32.p, m->tobj_d.p, m->tri_d.p,
-                                       T, split_len, make_coef<float>(k0, nf),
-                                       interior_table<float>(m, nf, k0), m->partial.p, ck0, ck1,
-                                       multi);
-        else
-            dispatch_far<float, true>(grid, blk, s, m->geo32.p, m->dyn32.p, m->tobj_d.p, m->tri_d.p,
-                                      T, split_len, make_coef<float>(k0, nf),
-                                      interior_table<float>(m, nf, k0), m->partial.p, ck0, ck1,
-                                      multi);
-        BEM_LAUNCH_CHECK();
+        const SymRound &last = sp.rounds.back();
+        hipLaunchKernelGGL(reduce_sym_kernel, gr, dim3(256), 0, s, ptau, psig, last.sig_base, last.b0,
+                           last.b1, sigacc, m->tst.p, T, blk, sp.chunk, m->trirows.p);
     } else {
-        if (m->dyn64.n < (size_t)T * DYN_STRIDE) m->dyn64.alloc((size_t)T * DYN_STRIDE);
-        hipLaunchKernelGGL(source_gather_kernel<double>, gg, dim3(256), 0, s, m->tri_d.p,
-                           m->tst.p, x, m->N, T, m->dyn64.p);
-        BEM_LAUNCH_CHECK();
-        Timer tm("farfield_fp64", s);
-        dispatch_far<double, true>(grid, blk, s, m->geo64.p, m->dyn64.p, m->tobj_d.p, m->tri_d.p, T, split_len,
-                             make_coef<double>(k0, nf), interior_table<double>(m, nf, k0), m->partial.p, ck0,
-                             ck1, multi);
-        BEM_LAUNCH_CHECK();
-    }
-    if (!sym) {
-        hipLaunchKernelGGL(reduce_splits_kernel, gg, dim3(256), 0, s, m->partial.p, m->tst.p,
-                           T, nsplit, m->trirows.p);
-        BEM_LAUNCH_CHECK();
+        const int nsplit = plan.nsplit, split_len = (T + nsplit - 1) / nsplit;
+        const size_t need = (size_t)nsplit * T * (ROW_STRIDE + 6);
+        if (m->partial.n < need) m->partial.alloc(need);
+        const dim3 grid((T + blk - 1) / blk, nsplit);
+        const bool ck0 = plan.code & 4, ck1 = plan.code & 2, multi = plan.code & 1;
+        {
+            Timer tm(name, s);
+            if (F32 && !plan.fr)
+                dispatch_far<R, !F32>(grid, blk, s, geo, dyn, m->tobj_d.p, m->tri_d.p, T, split_len,
+                                      cf, it, m->partial.p, ck0, ck1, multi);
+            else
+                dispatch_far<R, true>(grid, blk, s, geo, dyn, m->tobj_d.p, m->tri_d.p, T, split_len,
+                                      cf, it, m->partial.p, ck0, ck1, multi);
+        }
+        hipLaunchKernelGGL(reduce_splits_kernel, gg, dim3(256), 0, s, m->partial.p, m->tst.p, T, nsplit,
+                           m->trirows.p);
     }
     Timer tf("finalize", s);
-    hipLaunchKernelGGL(finalize_kernel, dim3((m->N + 255) / 256), dim3(256), 0, s,
-                       m->trirows.p, m->star_ptr.p, m->star_idx.p, m->nf_rowptr.p,
-                       m->nf_col.p, (const double2 *)nf.vals.p, m->nf_nnz, x, m->N, y);
-    BEM_LAUNCH_CHECK();
-}
-
-namespace {
-
-// NR right-hand sides through the multi-vector kernel (FP32 without phase
-// reduction, or FP64).
-template <class R, int NR>
-void farfield_multi_apply(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
-                          double rho, int code, int blk, const double2 *x, double2 *y,
-                          hipStream_t s) {
-    constexpr bool F32 = std::is_same<R, float>::value;
-    const int T = (int)m->T;
-    const int64_t N = m->N, n2 = 2 * N;
-    const int nsplit = farfield_splits(T, far_slots(multi_kernel<R, NR>(code), blk, 0), blk);
-    const int split_len = (T + nsplit - 1) / nsplit;
-    const int64_t rstride = (int64_t)nsplit * T * (ROW_STRIDE + 6);
-    if (m->partial.n < (size_t)(NR * rstride)) m->partial.alloc((size_t)(NR * rstride));
-    if (m->trirows.n < (size_t)T * ROW_STRIDE) m->trirows.alloc((size_t)T * ROW_STRIDE);
-    R *dyn;
-    if constexpr (F32) {
-        if (m->dyn32.n < (size_t)NR * T * DYN_STRIDE) m->dyn32.alloc((size_t)NR * T * DYN_STRIDE);
-        dyn = m->dyn32.p;
-    } else {
-        if (m->dyn64.n < (size_t)NR * T * DYN_STRIDE) m->dyn64.alloc((size_t)NR * T * DYN_STRIDE);
-        dyn = m->dyn64.p;
-    }
-    const R *geo = F32 ? (const R *)m->geo32.p : (const R *)m->geo64.p;
-    dim3 gg((T + 255) / 256);
-    for (int r = 0; r < NR; r++) {
-        hipLaunchKernelGGL(source_gather_kernel<R>, gg, dim3(256), 0, s, m->tri_d.p, m->tst.p,
-                           x + r * n2, N, T, dyn + (int64_t)r * T * DYN_STRIDE);
-        BEM_LAUNCH_CHECK();
-    }
-    {
-        Timer tm(F32 ? "farfield_fp32_multi" : "farfield_fp64_multi", s);
-        launch_multi<R, NR>(code, dim3((T + blk - 1) / blk, nsplit), blk, s, geo, dyn,
-                            m->tobj_d.p, m->tri_d.p, T, split_len, make_coef<R>(k0, nf),
-                            interior_table<R>(m, nf, k0), m->partial.p);
-        BEM_LAUNCH_CHECK();
-    }
-    for (int r = 0; r < NR; r++) {
-        hipLaunchKernelGGL(reduce_splits_kernel, gg, dim3(256), 0, s, m->partial.p + r * rstride,
-                           m->tst.p, T, nsplit, m->trirows.p);
-        BEM_LAUNCH_CHECK();
-        hipLaunchKernelGGL(finalize_kernel, dim3((N + 255) / 256), dim3(256), 0, s, m->trirows.p,
-                           m->star_ptr.p, m->star_idx.p, m->nf_rowptr.p, m->nf_col.p,
-                           (const double2 *)nf.vals.p, m->nf_nnz, x + r * n2, N, y + r * n2);
-        BEM_LAUNCH_CHECK();
-    }
+    hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((m->N * NEAR_LANES + 255) / 256)), dim3(256), 0, s,
+                       m->trirows.p, m->star_ptr.p, m->star_idx.p, m->nf_rowptr.p, m->nf_col.p,
+                       (const double2 *)nf.vals.p, m->nf_nnz, x, m->N, y);
 }
 
 }   // namespace
+
+void farfield_apply(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
+                    double rho, const double2 *x, double2 *y, int precision,
+                    hipStream_t s, int block) {
+    const FarPlan plan = far_plan(m, precision, k0, nf.k1_plan,
+                                  valid_block(block > 0 ? block : tune_lookup(m->T, 1).block));
+    if (precision == BEM_FP32) far_apply<float>(m, nf, k0, plan, x, y, s);
+    else far_apply<double>(m, nf, k0, plan, x, y, s);
+}
 
 void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
                           double rho, const double2 *x, double2 *y, int R, int precision,
@@ -1787,15 +1687,6 @@ void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, doubl
             const int nr = std::min(most, R - r0);
             farfield_mx_apply(m, nf, k0, x + r0 * n2, y + r0 * n2, nr, precision, s);
             r0 += nr;
-        }
-        if (R - r0 == 2) {
-            const double2 *xr = x + r0 * n2;
-            double2 *yr = y + r0 * n2;
-            if (precision == BEM_FP32)
-                farfield_multi_apply<float, 2>(m, nf, k0, k1, rho, plan.code, blk, xr, yr, s);
-            else
-                farfield_multi_apply<double, 2>(m, nf, k0, k1, rho, plan.code, blk, xr, yr, s);
-            r0 += 2;
         }
     }
     for (; r0 < R; r0++)
