@@ -508,14 +508,13 @@ int bem_profile_read(const char *kernel, double *total_ms, int64_t *launches);
  *                         MiB (1..65536, default 4096: one launch up to about
  *                         60 000 vertices); larger meshes run the test blocks
  *                         in several launches, results unchanged
- *   "dense.skinny_min_rhs" right-hand-side count (>= 2) from which products
- *                         with the assembled operator below gemm_min use the
- *                         16-column MFMA kernel instead of the multi-vector
- *                         GEMV (default 24: not below the default gemm_min)
+ *   "dense.skinny_min_rhs" accepted and returned, without effect: products with
+ *                         the assembled operator below gemm_min take the
+ *                         vector or the matrix units by their count
  *   "dense.gemm_min_rhs"  right-hand-side count from which the assembled
- *                         operator is applied with the MFMA product instead of
- *                         the multi-vector product, 8 vectors per pass
- *                         (default 24)
+ *                         operator is applied with the MFMA GEMM instead of
+ *                         the products that read the operator once per 32
+ *                         vectors (default 33)
  *   "solve.refine_update" FP32 refinement (precision BEM_FP32 in
  *                         pmchwt_solve): 1 forms the first outer residual
  *                         b - P64 x with the FP64 operator and updates the
@@ -591,10 +590,10 @@ int bem_hmat_info(const bem_mesh *mesh, bem_c64 k_ext, bem_c64 k_int, double rho
 /*
  * Autotuner.  For a mesh size (triangle count) and a right-hand-side count it
  * times, on the device, the pair-kernel workgroup size (64, 128 or 256 test
- * triangles) and the right-hand sides per launch (1, 2, 4) of the FP32
+ * triangles) and the right-hand sides per launch (one or shared) of the FP32
  * matrix-free operator, and, when the assembled complex64 operator fits in
  * free device memory with 2 GiB to spare, its assembly and the product with
- * n_rhs vectors (multi-vector GEMV, 16-column MFMA kernel or MFMA GEMM).  The
+ * n_rhs vectors (up to 32 per pass, or MFMA GEMM).  The
  * assembled path is chosen when assembly + expected_matvecs products beat
  * expected_matvecs matrix-free applications.  The result is kept for (n_triangles, bucket of n_rhs:
  * 1, 2-3, 4-7, 8-15, 16+) and used by every later matvec and solve of that
@@ -607,8 +606,7 @@ typedef struct {
     int block;               /* test triangles per pair-kernel workgroup */
     int multi;               /* right-hand sides per pair-kernel launch */
     int gemm_min;            /* assembled path: MFMA GEMM from this many vectors */
-    int skinny_min;          /* below gemm_min: 16-column MFMA product from this many, else
-                                the multi-vector GEMV */
+    int skinny_min;          /* without effect */
     int path;                /* -1 no preference, 0 matrix-free, 1 assembled */
     double t_matrix_free;    /* seconds per operator application to n_rhs vectors */
     double t_assembled;      /* same on the assembled operator (0 if not timed) */

@@ -274,7 +274,7 @@ struct bem_mesh {
     std::map<bem::NearKey, std::unique_ptr<bem::DenseOperator>> dense_rounded_cache;   // of dense64
     std::map<bem::NearKey, std::unique_ptr<bem::HMatrix, bem::HMatDeleter>> hmat_cache;
     std::shared_ptr<bem::DenseShare> dense_share;   // set for serving replicas
-    bem::DevBuf<float2> xs32;          // complex64 copy of a matvec input
+    bem::DevBuf<float2> xs32;          // scratch of the assembled products
 
     // OSRC: P1 vertex graph, M and S values, factor state per parameter set
     std::unique_ptr<bem::OsrcSymbolicState, bem::OsrcSymDeleter> osrc_sym;
@@ -306,8 +306,8 @@ struct Tuning {
     std::atomic<int> farfield_block{256};     // test triangles per pair-kernel workgroup
     std::atomic<int> farfield_symmetric{1};   // single vector: each separated pair once
     std::atomic<int> farfield_sym_round_mib{4096};   // symmetric kernel: sigma partials per launch
-    std::atomic<int> dense_gemm_min_rhs{24};  // MFMA product from this many right-hand sides
-    std::atomic<int> dense_skinny_min_rhs{24}; // skinny MFMA product from this many (else multi-GEMV)
+    std::atomic<int> dense_gemm_min_rhs{33};  // MFMA GEMM from this many right-hand sides
+    std::atomic<int> dense_skinny_min_rhs{24}; // kept for callers that set it: the count decides
     std::atomic<int> solve_refine_update{1};  // FP32 refinement: later residuals updated in FP32
     std::atomic<int> solve_residual_dense_gib{32};   // complex128 operator for FP32-path residuals
     // compressed operator (read when one is built)
@@ -330,8 +330,8 @@ Tuning &tuning();
 struct TuneEntry {
     int block = 256;           // test triangles per pair-kernel workgroup: 64, 128, 256
     int multi = 4;             // 1: one right-hand side per pair-kernel launch; 2, 4: shared
-    int gemm_min = 24;         // MFMA product from this many right-hand sides
-    int skinny_min = 24;       // below gemm_min: skinny MFMA product from this many, else multi-vector GEMV
+    int gemm_min = 33;         // MFMA GEMM from this many right-hand sides
+    int skinny_min = 24;       // without effect (kept in the saved lines)
     int path = -1;             // FP32 solves: -1 no preference, 0 matrix-free, 1 assembled
     double t_mf = 0, t_dense = 0, t_asm = 0;   // seconds (R vectors; assembly)
 };
@@ -415,10 +415,12 @@ std::unique_ptr<DenseOperator> dense_assemble(bem_mesh *m, const NearOperator &n
 // complex64 one)
 const DenseOperator &dense_get(bem_mesh *m, double2 k0, double2 k1, double rho, hipStream_t s,
                                int s1 = 1, const ObjMaterials *om = nullptr, bool fp64 = false);
-// y_r = B x_r, r < R (x, y RHS-major [R][2N]): multi-vector product reading B
-// once per 8 right-hand sides
+// y_r = B x_r, r < R (x, y RHS-major [R][2N]): product reading B once per 32
+// right-hand sides, scratch in xs
 void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DevBuf<float2> &xs,
-                hipStream_t s, bool skinny = true);
+                hipStream_t s);
+// scratch of the product of R >= 2 right-hand sides below the MFMA GEMM's count
+int64_t dense_mx_scratch_bytes(int64_t N, int R, bool fp64);
 // Y = B X for R right-hand sides (x, y RHS-major [R][2N]) on MFMA
 void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hipStream_t s);
 int64_t dense_gemm_scratch_bytes(const bem_mesh *m, int R);

@@ -26,6 +26,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
+#include <mutex>
 
 #include "bem_internal.h"
 #include "entries.h"
@@ -241,54 +243,66 @@ __global__ __launch_bounds__(256) void dense_gemv64_kernel(const double2 *__rest
         for (int q = 0; q < nrow; q++) y[row0 + q] = make_double2(sr[q], si[q]);
 }
 
-// y_r = B x_r for NR vectors (2..8); x: [NR][n2] complex64, y_r = y + r ystride.
-// Two rows per wavefront, GV_WAVES wavefronts per workgroup; each chunk of the
-// NR vectors (512 entries each) is staged in LDS once per workgroup and read by
-// all its rows (each LDS value once per wavefront, for both of its rows), so x
-// costs the L2 one pass per 2 GV_WAVES rows.  16-byte loads of B (2N even:
-// rows and vectors 16-byte aligned), non-temporal; FP32 partial sums per chunk
-// added in FP64, fixed-order wave reduction.
+// y_r = B x_r for NR vectors (2..7); x: [NR][n2] complex64, y_r = y + r ystride.
+// Bound by HBM if the loads of B never wait.  Two rows per wavefront; each chunk of
+// the NR vectors is staged in LDS by the workgroup and read by all its rows (each
+// LDS value once per wavefront, for both of its rows).  Up to five vectors the next
+// chunk of both is in flight while one is multiplied (two and four vectors on 5 124
+// rows 43 and 51 us, without 52 and 64; on 20 484 rows 541 and 607, 570 and 610);
+// beyond, the registers do not allow it, and longer chunks and more wavefronts per
+// workgroup are the faster form.  16-byte loads of B (2N even: rows and vectors
+// 16-byte aligned), non-temporal; FP32 partial sums per chunk added in FP64,
+// fixed-order wave reduction.
 constexpr int GV_RW = 2;      // rows per wavefront
-constexpr int GV_CH = 256;    // float4 (two complex entries) per chunk and vector
-constexpr int GV_WAVES = 8;   // wavefronts per workgroup
+template <int NR> constexpr bool gv_ahead() { return NR <= 5; }
+template <int NR> constexpr int gv_chunk() { return gv_ahead<NR>() ? 128 : 256; }   // float4 per vector
+template <int NR> constexpr int gv_waves() { return gv_ahead<NR>() ? 4 : 8; }       // per workgroup
 
 template <int NR>
-__global__ __launch_bounds__(64 * GV_WAVES) void dense_gemv_kernel(const float2 *__restrict__ B,
-                                                                   int64_t n2,
-                                                                   const float2 *__restrict__ x,
-                                                                   double2 *__restrict__ y,
-                                                                   int64_t ystride) {
-    constexpr int NT = 64 * GV_WAVES, NU = GV_CH / 64;
-    __shared__ fvec4 xs[NR * GV_CH];
+__global__ __launch_bounds__(64 * gv_waves<NR>()) void dense_gemv_kernel(
+    const float2 *__restrict__ B, int64_t n2, const float2 *__restrict__ x, double2 *__restrict__ y,
+    int64_t ystride) {
+    constexpr bool AHEAD = gv_ahead<NR>();
+    constexpr int CH = gv_chunk<NR>(), NT = 64 * gv_waves<NR>(), NU = CH / 64,
+                  NX = (NR * CH + NT - 1) / NT;
+    __shared__ fvec4 xs[AHEAD ? 2 : 1][NR * CH];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t row0 = ((int64_t)blockIdx.x * GV_WAVES + wave) * GV_RW;
+    const int64_t row0 = ((int64_t)blockIdx.x * gv_waves<NR>() + wave) * GV_RW;
     const int nrow = row0 >= n2 ? 0 : (n2 - row0 < GV_RW ? (int)(n2 - row0) : GV_RW);
     const fvec4 *b4[GV_RW];
     for (int q = 0; q < GV_RW; q++)
         b4[q] = reinterpret_cast<const fvec4 *>(B + (q < nrow ? row0 + q : 0) * n2);
     const fvec4 *x4 = reinterpret_cast<const fvec4 *>(x);
     const int64_t n4 = n2 / 2;
-    double sr[GV_RW][NR], si[GV_RW][NR];
-    for (int q = 0; q < GV_RW; q++)
-        for (int r = 0; r < NR; r++) sr[q][r] = si[q][r] = 0.0;
-    for (int64_t c0 = 0; c0 < n4; c0 += GV_CH) {
-        const int cnt = n4 - c0 < GV_CH ? (int)(n4 - c0) : GV_CH;
-        __syncthreads();   // the previous chunk's readers are done
-        for (int idx = threadIdx.x; idx < NR * GV_CH; idx += NT) {
-            const int r = idx / GV_CH, c = idx - r * GV_CH;
-            xs[idx] = c < cnt ? x4[r * n4 + c0 + c] : fvec4{0.f, 0.f, 0.f, 0.f};
-        }
-        __syncthreads();
-        if (nrow == 0) continue;   // (the barriers above stay uniform)
-        fvec4 a[GV_RW][NU];
+    const fvec4 zero = fvec4{0.f, 0.f, 0.f, 0.f};
+    auto load_b = [&](int64_t c0, fvec4 (&a)[GV_RW][NU]) {
 #pragma unroll
         for (int q = 0; q < GV_RW; q++)
 #pragma unroll
             for (int u = 0; u < NU; u++) {
-                const int c = u * 64 + lane;
-                a[q][u] = c < cnt ? __builtin_nontemporal_load(b4[q] + c0 + c)
-                                  : fvec4{0.f, 0.f, 0.f, 0.f};
+                const int64_t c = c0 + u * 64 + lane;
+                a[q][u] = c < n4 ? __builtin_nontemporal_load(b4[q] + c) : zero;
             }
+    };
+    auto load_x = [&](int64_t c0, fvec4 (&v)[NX]) {
+#pragma unroll
+        for (int w = 0; w < NX; w++) {
+            const int idx = w * NT + threadIdx.x, r = idx / CH;
+            const int64_t c = c0 + (idx - r * CH);
+            v[w] = r < NR && c < n4 ? x4[r * n4 + c] : zero;
+        }
+    };
+    auto store_x = [&](int buf, const fvec4 (&v)[NX]) {
+#pragma unroll
+        for (int w = 0; w < NX; w++) {
+            const int idx = w * NT + threadIdx.x;
+            if (idx < NR * CH) xs[buf][idx] = v[w];
+        }
+    };
+    double sr[GV_RW][NR], si[GV_RW][NR];
+    for (int q = 0; q < GV_RW; q++)
+        for (int r = 0; r < NR; r++) sr[q][r] = si[q][r] = 0.0;
+    auto multiply = [&](int buf, const fvec4 (&a)[GV_RW][NU]) {
 #pragma unroll
         for (int r = 0; r < NR; r++) {
             float pr[GV_RW], pi[GV_RW];
@@ -296,7 +310,7 @@ __global__ __launch_bounds__(64 * GV_WAVES) void dense_gemv_kernel(const float2 
             for (int q = 0; q < GV_RW; q++) pr[q] = pi[q] = 0.f;
 #pragma unroll
             for (int u = 0; u < NU; u++) {
-                const fvec4 v = xs[r * GV_CH + u * 64 + lane];
+                const fvec4 v = xs[buf][r * CH + u * 64 + lane];
 #pragma unroll
                 for (int q = 0; q < GV_RW; q++) {
                     pr[q] += a[q][u].x * v.x - a[q][u].y * v.y;
@@ -310,6 +324,40 @@ __global__ __launch_bounds__(64 * GV_WAVES) void dense_gemv_kernel(const float2 
                 sr[q][r] += pr[q];
                 si[q][r] += pi[q];
             }
+        }
+    };
+    fvec4 a[GV_RW][NU], xv[NX];
+    if constexpr (AHEAD) {
+        fvec4 an[GV_RW][NU];
+        load_x(0, xv);
+        load_b(0, a);
+        store_x(0, xv);
+        __syncthreads();
+        int buf = 0;
+        for (int64_t c0 = 0; c0 < n4; c0 += CH, buf ^= 1) {
+            const bool more = c0 + CH < n4;   // (uniform)
+            if (more) {
+                load_x(c0 + CH, xv);
+                load_b(c0 + CH, an);
+            }
+            multiply(buf, a);
+            if (more) {
+                store_x(buf ^ 1, xv);   // (its readers passed the previous barrier)
+#pragma unroll
+                for (int q = 0; q < GV_RW; q++)
+#pragma unroll
+                    for (int u = 0; u < NU; u++) a[q][u] = an[q][u];
+            }
+            __syncthreads();
+        }
+    } else {
+        for (int64_t c0 = 0; c0 < n4; c0 += CH) {
+            __syncthreads();   // the previous chunk's readers are done
+            load_x(c0, xv);
+            store_x(0, xv);
+            __syncthreads();
+            load_b(c0, a);
+            multiply(0, a);
         }
     }
     if (nrow == 0) return;
@@ -531,102 +579,197 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float *__restric
     y[(int64_t)r * M + m] = make_double2(sr, si);
 }
 
-// ------------------------------------ 2-8 right-hand sides: skinny MFMA product
-// The same real GEMM with 16 columns (8 complex right-hand sides) on
-// v_mfma_f32_16x16x4f32.  HBM-bound: every wave streams blocks of 16 rows of
-// B over its K chunk, 1 KB of each row per step, with load instructions that
-// read 64 contiguous bytes of each of the 16 rows (the four lanes q of a row
-// are adjacent): long per-row runs keep HBM streaming.  The operand is the
-// transposed, re/im interleaved XT[16][Kp].  The 4 k-slots of an MFMA may
-// hold any 4 values of k as long as A and XT agree: in a step of 256, lane
-// (i, q) = (lane % 16, lane / 16) holds k = kb + 16c + 4q + e (c < 16, e < 4)
-// and MFMA (c, e) takes component e of its c-th 16-byte load.
-constexpr int SK_ROWS = 256;    // rows per workgroup (4 waves x 4 blocks of 16)
-constexpr int SK_KC = 1024;     // split-K chunk (real K): FP32 accumulation length
+// ----------------------------- up to 32 right-hand sides: skinny MFMA product
+// The same real product with 16 NT columns (8 NT complex right-hand sides) on
+// v_mfma_f32_16x16x4 / v_mfma_f64_16x16x4, for the complex64 and the complex128
+// operator.  Bound by HBM (every entry of B once per launch); the matrix cores
+// need 0.18 ms for 8 vectors at 10 242 vertices, B 0.52 ms at the rate of the
+// one-vector product.  A wavefront streams 16 RT rows over its range of K with
+// 16-byte loads of 256 or 512 contiguous bytes a row, the next step's loads in
+// flight, and turns them through LDS (loads in the operand's own order read 64
+// bytes a row, 20 % slower; 8 vectors on the vector units took 1.10 ms, complex128
+// one by one 8.3 ms, here 1.24);
+// the columns come from XT[16 NT][Kp] through the caches.  The 4 k-slots of a matrix instruction may hold any 4 values of k as
+// long as A and XT agree: lane (i, q) = (lane % 16, lane / 16) holds VE values of
+// row i from k = kb + VE (4 c + q) on, and instruction (c, e) takes the e-th.
+template <class R> struct MxOp;
+template <> struct MxOp<float> {
+    typedef float Vec __attribute__((ext_vector_type(4)));
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static constexpr int VE = 4;
+    static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
+};
+template <> struct MxOp<double> {
+    typedef double Vec __attribute__((ext_vector_type(2)));
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    static constexpr int VE = 2;
+    static __device__ __forceinline__ Acc mma(double a, double b, Acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int lane, int v) { return (lane >> 4) + 4 * v; }
+};
+// lanes along a row per load: 16 for the complex64 operator (10 242 vertices, 8
+// and 32 vectors: 0.735 and 1.23 ms, with 32 lanes 0.762 and 1.47), 32 for the
+// complex128 one while the columns leave room (8 vectors 1.24 against 1.30 ms)
+template <class R, int NT> constexpr int mx_lpr() {
+    return std::is_same<R, double>::value && NT <= 2 ? 32 : 16;
+}
+// waves per SIMD asked for (registers)
+template <class R, int NT> constexpr int mx_waves() {
+    return NT > 2 ? 1 : std::is_same<R, double>::value ? 2 : 3;
+}
+// Type of the products and sums.  The complex64 operator's up to 16 vectors are
+// FP64 (exact products of FP32 values): FP32 matrix instructions add four products
+// into the sum each, and even sums of 8 products had an error above that of the
+// vector units (1.4e-7 against 1.3e-7, 1.9e-7 for sums of 64); FP64 gives
+// 1.2e-7, and B still costs more than the matrix cores (0.42 ms for 8 vectors).  Beyond, FP32 in
+// sums of 64 added in FP64, as against 8.6e-7 of the MFMA GEMM it took over from.
+template <class R, int NT>
+using MxWork = std::conditional_t<std::is_same<R, double>::value || NT <= 2, double, float>;
+template <class R, int NT> constexpr int mx_step() { return MxOp<R>::VE * mx_lpr<R, NT>(); }   // of K
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-// XT[2r][2k], XT[2r][2k+1], XT[2r+1][2k], XT[2r+1][2k+1] from x[r][k], r < R <= 8
-__global__ __launch_bounds__(256) void skinny_xprep_kernel(const double2 *__restrict__ x, int R,
-                                                           int64_t K, float *__restrict__ XT) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= K * 8) return;
-    const int r = (int)(id / K);
-    const int64_t k = id - (int64_t)r * K;
-    const double2 v = r < R ? x[(int64_t)r * K + k] : make_double2(0.0, 0.0);
-    const int64_t Kp = 2 * K;
-    float *re = XT + (2 * r) * Kp, *im = re + Kp;
-    re[2 * k] = (float)v.x;
-    re[2 * k + 1] = (float)(-v.y);
-    im[2 * k] = (float)v.y;
-    im[2 * k + 1] = (float)v.x;
+// XT[2r][2k], XT[2r][2k+1] = Re, -Im and XT[2r+1][..] = Im, Re of x[r][k]; zeros
+// for r >= nr (r < 8 NT)
+template <class R>
+__global__ __launch_bounds__(256) void mx_prep_kernel(const double2 *__restrict__ x, int nr,
+                                                      int64_t K, R *__restrict__ XT) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int r = blockIdx.y;
+    if (k >= K) return;
+    const double2 v = r < nr ? x[(int64_t)r * K + k] : make_double2(0.0, 0.0);
+    R *re = XT + (int64_t)(2 * r) * 2 * K, *im = re + 2 * K;
+    re[2 * k] = (R)v.x;
+    re[2 * k + 1] = (R)(-v.y);
+    im[2 * k] = (R)v.y;
+    im[2 * k + 1] = (R)v.x;
 }
 
-// Yp[chunk][M][16] partial products; grid (ceil(M / 256), chunks).  The
-// workgroup's XT chunk [16][SK_KC] is staged in LDS once; every wave streams
-// 4 blocks of 16 rows, block by block, 1 KB of each row per step.
-__global__ __launch_bounds__(256) void skinny_mfma_kernel(const float *__restrict__ A,
-                                                          const float *__restrict__ XT,
-                                                          float *__restrict__ Yp, int64_t M,
-                                                          int64_t Kp) {
-    // rows padded by 4 floats: the 16 rows' 16-byte reads fall in distinct banks
-    constexpr int XS = SK_KC + 4;
-    __shared__ float xs[16 * XS];
+// part[blockIdx.y][M][16 NT]; grid (ceil(M / (64 RT)), ranges of klen)
+template <class R, int RT, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mx_waves<R, NT>()))) void mx_gemv_kernel(const R *__restrict__ A,
+                                                      const R *__restrict__ XT,
+                                                      double *__restrict__ part, int64_t M,
+                                                      int64_t Kp, int64_t klen) {
+    using WT = MxWork<R, NT>;
+    using O = MxOp<WT>;
+    using Vec = typename MxOp<R>::Vec;
+    constexpr int VE = MxOp<R>::VE, STEP = mx_step<R, NT>();
+    constexpr int LPR = mx_lpr<R, NT>(), UC = LPR / 4;   // UC loads per tile and step
+    constexpr bool F32 = std::is_same<WT, float>::value;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = lane & 15, q = lane >> 4;
-    const int64_t kbeg = (int64_t)blockIdx.y * SK_KC;
-    const int64_t kend = kbeg + SK_KC < Kp ? kbeg + SK_KC : Kp;
-    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int idx = threadIdx.x; idx < 16 * SK_KC / 4; idx += 256) {
-        const int c = idx / (SK_KC / 4), k4 = 4 * (idx - c * (SK_KC / 4));
-        *(float4 *)&xs[c * XS + k4] =
-            kbeg + k4 < kend ? *(const float4 *)(XT + (int64_t)c * Kp + kbeg + k4) : zero4;
-    }
-    __syncthreads();
-    floatx4 acc[4];
-    for (int b = 0; b < 4; b++)
-        for (int v = 0; v < 4; v++) acc[b][v] = 0.f;
-    const int64_t rbase = (int64_t)blockIdx.x * SK_ROWS + wave * 64;
-    // units u = (step, block): 16 rows x 256 k; the next unit's 16 loads are
-    // issued before this unit's 64 MFMAs
-    const int nsteps = (int)((kend - kbeg + 255) / 256);
-    auto load = [&](int u, float4 (&a)[16]) {
-        const int64_t kb = kbeg + 256 * (int64_t)(u >> 2);
-        const int64_t row = rbase + 16 * (u & 3) + i;
-        const bool rin = row < M;
-        const float *arow = A + (rin ? row : 0) * Kp;
-        for (int c = 0; c < 16; c++) {
-            const int64_t kk = kb + 16 * c + 4 * q;   // multiple of 4, as are kend and Kp
-            a[c] = (rin && kk < kend) ? *(const float4 *)(arow + kk) : zero4;
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * 16 * RT;
+    const int64_t kbeg = (int64_t)blockIdx.y * klen;
+    const int64_t kend = kbeg + klen < Kp ? kbeg + klen : Kp;
+    if (row0 >= M) return;
+    // this wavefront's 16 RT rows of one step, padded: the 16 lanes of a read (one
+    // value of q) fall in distinct banks
+    constexpr int LDR = LPR * VE + 16 / (int)sizeof(R);
+    __shared__ R stage[4][RT * 16 * LDR];
+    R *st = stage[wave];
+    const R *xrow[NT];
+    for (int n = 0; n < NT; n++) xrow[n] = XT + (int64_t)(16 * n + i) * Kp;
+    const Vec zero = (Vec)(R)0;
+    // load c of tile t: rows (64 / LPR) c + lr, LPR lanes of 16 bytes along each
+    const int lv = lane % LPR, lr = lane / LPR;
+    auto load_a = [&](int64_t kb, Vec (&v)[RT][UC]) {
+        const int64_t k = kb + VE * lv;   // (K is a multiple of VE)
+#pragma unroll
+        for (int t = 0; t < RT; t++)
+#pragma unroll
+            for (int c = 0; c < UC; c++) {
+                const int64_t r = row0 + 16 * t + 64 / LPR * c + lr;   // (rows beyond the end are not stored)
+                v[t][c] = k < kend ? *(const Vec *)(A + (r < M ? r : M - 1) * Kp + k) : zero;
+            }
+    };
+    typename O::Acc acc[RT][NT];
+    double sum[RT][NT][4];
+    for (int t = 0; t < RT; t++)
+        for (int n = 0; n < NT; n++)
+            for (int v = 0; v < 4; v++) acc[t][n][v] = (WT)0, sum[t][n][v] = 0.0;
+    auto flush = [&]() {   // FP32 sums into the FP64 ones
+        if constexpr (F32) {
+#pragma unroll
+            for (int t = 0; t < RT; t++)
+#pragma unroll
+                for (int n = 0; n < NT; n++)
+#pragma unroll
+                    for (int v = 0; v < 4; v++) {
+                        sum[t][n][v] += (double)acc[t][n][v];
+                        acc[t][n][v] = (WT)0;
+                    }
         }
     };
-    float4 av[16], an[16], bv[16];
-    load(0, av);
-    for (int st = 0; st < nsteps; st++) {
-        for (int c = 0; c < 16; c++)
-            bv[c] = *(const float4 *)&xs[i * XS + 256 * st + 16 * c + 4 * q];
+    Vec an[RT][UC];
+    load_a(kbeg, an);
+    for (int64_t kb = kbeg; kb < kend; kb += STEP) {
+        const bool more = kb + STEP < kend;
 #pragma unroll
-        for (int b = 0; b < 4; b++) {
-            const int u = 4 * st + b;
-            const bool more = u + 1 < 4 * nsteps;
-            if (more) load(u + 1, an);
-            for (int c = 0; c < 16; c++) {
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c].x, bv[c].x, acc[b], 0, 0, 0);
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c].y, bv[c].y, acc[b], 0, 0, 0);
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c].z, bv[c].z, acc[b], 0, 0, 0);
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c].w, bv[c].w, acc[b], 0, 0, 0);
+        for (int t = 0; t < RT; t++)
+#pragma unroll
+            for (int c = 0; c < UC; c++)
+                *(Vec *)(st + (16 * t + 64 / LPR * c + lr) * LDR + VE * lv) = an[t][c];
+        // (only this wavefront's lanes read them: LDS serves a wavefront in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (more) load_a(kb + STEP, an);
+#pragma unroll
+        for (int c0 = 0; c0 < UC; c0 += 4) {
+            Vec av[RT][4], bv[NT][4];
+#pragma unroll
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    const int64_t k = kb + VE * (4 * (c0 + c) + q);
+                    bv[n][c] = k < kend ? *(const Vec *)(xrow[n] + k) : zero;
+                }
+#pragma unroll
+            for (int t = 0; t < RT; t++)
+#pragma unroll
+                for (int c = 0; c < 4; c++)
+                    av[t][c] = *(const Vec *)(st + (16 * t + i) * LDR + VE * (4 * (c0 + c) + q));
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+#pragma unroll
+                for (int e = 0; e < VE; e++) {
+#pragma unroll
+                    for (int t = 0; t < RT; t++)
+#pragma unroll
+                        for (int n = 0; n < NT; n++)
+                            acc[t][n] = O::mma((WT)av[t][c][e], (WT)bv[n][c][e], acc[t][n]);
+                }
             }
-            if (more)
-                for (int c = 0; c < 16; c++) av[c] = an[c];
+            flush();
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    // 16x16 accumulator layout: column lane % 16, row 4 (lane / 16) + v
-    float *Y = Yp + (int64_t)blockIdx.y * M * 16;
-    for (int b = 0; b < 4; b++) {
-        const int64_t r0 = rbase + 16 * b + 4 * q;
-        for (int v = 0; v < 4; v++)
-            if (r0 + v < M) Y[(r0 + v) * 16 + i] = acc[b][v];
+    double *out = part + (int64_t)blockIdx.y * M * 16 * NT;
+    for (int t = 0; t < RT; t++)
+        for (int v = 0; v < 4; v++) {
+            const int64_t r = row0 + 16 * t + O::row(lane, v);
+            if (r >= M) continue;
+            for (int n = 0; n < NT; n++)
+                out[r * 16 * NT + 16 * n + i] = F32 ? sum[t][n][v] : (double)acc[t][n][v];
+        }
+}
+
+// y[r][m] = sum over the ranges, in order, of part[.][m][2r], [2r + 1]
+__global__ __launch_bounds__(256) void mx_reduce_kernel(const double2 *__restrict__ part, int nsplit,
+                                                        int64_t M, int half, int nr,
+                                                        double2 *__restrict__ y) {
+    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t m = id / half;
+    const int r = (int)(id - m * half);
+    if (m >= M || r >= nr) return;
+    double2 v = make_double2(0.0, 0.0);
+    for (int sp = 0; sp < nsplit; sp++) {
+        const double2 p = part[(int64_t)sp * M * half + id];
+        v.x += p.x;
+        v.y += p.y;
     }
+    y[(int64_t)r * M + m] = v;
 }
 
 __global__ __launch_bounds__(256) void to_c64_kernel(const double2 *__restrict__ x,
@@ -802,30 +945,133 @@ std::unique_ptr<DenseOperator> dense_assemble(bem_mesh *m, const NearOperator &n
     return op;
 }
 
-template <int NR>
-void launch_gemv(const DenseOperator &op, const float2 *xs, double2 *y, hipStream_t s) {
-    const int64_t rows = (int64_t)GV_WAVES * GV_RW;   // per workgroup
-    hipLaunchKernelGGL(dense_gemv_kernel<NR>, dim3((unsigned)((op.n2 + rows - 1) / rows)),
-                       dim3(64 * GV_WAVES), 0, s, op.B.p, op.n2, xs, y, op.n2);
+namespace {
+
+constexpr int MX_MAX_RHS = 32;   // right-hand sides per launch of the skinny product
+
+int mx_tiles(int nr) { return nr <= 8 ? 1 : nr <= 16 ? 2 : 4; }
+
+constexpr int MX_RT = 2;        // 16-row tiles per wavefront
+constexpr int MX_SPLITS = 32;   // ranges of K at most
+
+// Ranges of K: all workgroups cost the same, so their number just fills whole
+// rounds of resident ones (a last round of a few cannot draw the memory's rate;
+// fixed ranges took 107 instead of 98 us on the 5 124-row complex128 operator).
+template <class R, int NT> int64_t mx_range(int64_t M, int64_t Kp) {
+    static std::mutex mu;
+    static std::map<int, int> cache;   // device -> resident workgroups
+    int dev = 0, slots = 0;
+    BEM_HIP(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> g(mu);
+        int &c = cache[dev];
+        if (c == 0) {
+            int cus = 0, per = 0;
+            BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+            BEM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per, (const void *)mx_gemv_kernel<R, MX_RT, NT>, 256, 0));
+            c = std::max(1, cus * per);
+        }
+        slots = c;
+    }
+    constexpr int64_t STEP = mx_step<R, NT>();
+    const int64_t rows = (M + 64 * MX_RT - 1) / (64 * MX_RT);
+    int64_t best = Kp;
+    double best_cost = 1e300;
+    for (int ns = 1; ns <= MX_SPLITS; ns++) {
+        const int64_t len = ((Kp + ns - 1) / ns + STEP - 1) / STEP * STEP;
+        const double rounds = std::ceil((double)rows * ((Kp + len - 1) / len) / slots);
+        const double cost = rounds * (len + 4.0 * STEP);   // + first loads and output
+        if (cost < best_cost * (1 - 1e-9)) {
+            best_cost = cost;
+            best = len;
+        }
+    }
+    return best;
 }
 
-constexpr int GEMV_MAX_RHS = 8;   // right-hand sides per multi-vector GEMV launch
+template <class R, int NT>
+void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, char *scratch,
+               hipStream_t s) {
+    const int64_t M = n2, Kp = 2 * n2;
+    const int64_t klen = mx_range<R, NT>(M, Kp);
+    const int nsplit = (int)((Kp + klen - 1) / klen);
+    R *XT = (R *)scratch;
+    double *part = (double *)(scratch + 16 * NT * Kp * (int64_t)sizeof(R));
+    hipLaunchKernelGGL(mx_prep_kernel<R>, dim3((unsigned)((n2 + 255) / 256), 8 * NT), dim3(256), 0, s, x,
+                       nr, n2, XT);
+    BEM_LAUNCH_CHECK();
+    {
+        Timer tm(std::is_same<R, float>::value ? "dense_skinny_mfma" : "dense_skinny_mfma64", s);
+        hipLaunchKernelGGL((mx_gemv_kernel<R, MX_RT, NT>),
+                           dim3((unsigned)((M + 64 * MX_RT - 1) / (64 * MX_RT)), nsplit), dim3(256), 0, s,
+                           B, XT, part, M, Kp, klen);
+        BEM_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(mx_reduce_kernel, dim3((unsigned)((M * 8 * NT + 255) / 256)), dim3(256), 0, s,
+                       (const double2 *)part, nsplit, M, 8 * NT, nr, y);
+    BEM_LAUNCH_CHECK();
+}
+
+// nr <= MX_MAX_RHS right-hand sides in one launch; scratch in xs
+template <class T>
+void mx_apply(const T *B, int64_t n2, const double2 *x, double2 *y, int nr, DevBuf<float2> &xs,
+              hipStream_t s) {
+    const size_t need = (size_t)dense_mx_scratch_bytes(n2 / 2, nr, sizeof(T) == 8) / sizeof(float2);
+    if (xs.n < need) xs.alloc(need);
+    switch (mx_tiles(nr)) {
+    case 1: mx_launch<T, 1>(B, n2, x, y, nr, (char *)xs.p, s); break;
+    case 2: mx_launch<T, 2>(B, n2, x, y, nr, (char *)xs.p, s); break;
+    default: mx_launch<T, 4>(B, n2, x, y, nr, (char *)xs.p, s); break;
+    }
+}
+
+// right-hand sides of the next launch when `left` remain: 24 to 32 share one (four
+// column tiles; below, 16 and the rest apart are no slower and keep short sums)
+int mx_group(int left) { return left >= 24 ? std::min(left, MX_MAX_RHS) : std::min(left, 16); }
+
+}   // namespace
+
+int64_t dense_mx_scratch_bytes(int64_t N, int R, bool fp64) {
+    const int64_t cols = 16 * mx_tiles(std::min(R, MX_MAX_RHS)), n2 = 2 * N;
+    return cols * 2 * n2 * (fp64 ? 8 : 4) + MX_SPLITS * n2 * cols * 8;
+}
+
+namespace {
+
+template <int NR>
+void launch_gemv(const DenseOperator &op, const float2 *xs, double2 *y, hipStream_t s) {
+    const int64_t rows = (int64_t)gv_waves<NR>() * GV_RW;   // per workgroup
+    hipLaunchKernelGGL(dense_gemv_kernel<NR>, dim3((unsigned)((op.n2 + rows - 1) / rows)),
+                       dim3(64 * gv_waves<NR>()), 0, s, op.B.p, op.n2, xs, y, op.n2);
+}
+
+// Vectors up to which the complex64 product runs on the vector units: five, or
+// seven on 10 000 rows and more, where they keep up with HBM.  us for 4, 5, 6, 7
+// vectors, vector and matrix units: 5 124 rows 50 54 72 78 and 62 for any number;
+// 10 584 rows 172 187 210 227 and 208; 20 484 rows 617 655 639 701 and 740.  At 8
+// the vector units need 1 104 us there.
+int gemv_max_rhs(int64_t n2) { return n2 >= 10000 ? 7 : 5; }
+
+}   // namespace
 
 void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DevBuf<float2> &xs,
-                hipStream_t s, bool skinny) {
+                hipStream_t s) {
     const int64_t n2 = op.n2;
-    if (R == 1 || !skinny) {
-        // multi-vector GEMV: one row per wavefront, B read once per 8 vectors
-        const int64_t need = (int64_t)std::min(R, GEMV_MAX_RHS) * n2;
-        if (xs.n < (size_t)need) xs.alloc((size_t)need);
-        for (int r0 = 0; r0 < R; r0 += GEMV_MAX_RHS) {
-            const int nr = std::min(GEMV_MAX_RHS, R - r0);
+    for (int r0 = 0; r0 < R;) {
+        const double2 *xr = x + r0 * n2;
+        double2 *yr = y + r0 * n2;
+        int nr = R - r0;
+        if (nr > gemv_max_rhs(n2)) {
+            nr = mx_group(nr);
+            mx_apply((const float *)op.B.p, n2, xr, yr, nr, xs, s);
+        } else {
             const int64_t cnt = nr * n2;
-            hipLaunchKernelGGL(to_c64_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0,
-                               s, x + r0 * n2, xs.p, cnt);
+            if (xs.n < (size_t)cnt) xs.alloc((size_t)cnt);
+            hipLaunchKernelGGL(to_c64_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, xr,
+                               xs.p, cnt);
             BEM_LAUNCH_CHECK();
             Timer tm("dense_gemv", s);
-            double2 *yr = y + r0 * n2;
             switch (nr) {
             case 1:
                 hipLaunchKernelGGL(dense_gemv1_kernel,
@@ -837,35 +1083,12 @@ void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, De
             case 4: launch_gemv<4>(op, xs.p, yr, s); break;
             case 5: launch_gemv<5>(op, xs.p, yr, s); break;
             case 6: launch_gemv<6>(op, xs.p, yr, s); break;
-            case 7: launch_gemv<7>(op, xs.p, yr, s); break;
-            default: launch_gemv<8>(op, xs.p, yr, s); break;
+            default: launch_gemv<7>(op, xs.p, yr, s); break;
             }
             BEM_LAUNCH_CHECK();
         }
-        return;
+        r0 += nr;
     }
-    const int64_t M = n2, Kp = 2 * n2;
-    const int nchunks = (int)((Kp + SK_KC - 1) / SK_KC);
-    DevBuf<float> XT((size_t)(16 * Kp));
-    DevBuf<float> Yp((size_t)nchunks * M * 16);
-    for (int r0 = 0; r0 < R; r0 += 8) {
-        const int nr = std::min(8, R - r0);
-        hipLaunchKernelGGL(skinny_xprep_kernel, dim3((unsigned)((8 * n2 + 255) / 256)), dim3(256),
-                           0, s, x + r0 * n2, nr, n2, XT.p);
-        BEM_LAUNCH_CHECK();
-        {
-            Timer tm("dense_skinny_mfma", s);
-            hipLaunchKernelGGL(skinny_mfma_kernel,
-                               dim3((unsigned)((M + SK_ROWS - 1) / SK_ROWS), nchunks), dim3(256),
-                               0, s, (const float *)op.B.p, XT.p, Yp.p, M, Kp);
-            BEM_LAUNCH_CHECK();
-        }
-        const int64_t red = M * nr;
-        hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((red + 255) / 256)), dim3(256), 0, s,
-                           Yp.p, nchunks, M, 16, nr, y + r0 * n2);
-        BEM_LAUNCH_CHECK();
-    }
-    BEM_HIP(hipStreamSynchronize(s));   // XT, Yp are released on return
 }
 
 int64_t dense_gemm_scratch_bytes(const bem_mesh *m, int R) {
@@ -906,19 +1129,27 @@ int gemm_kchunk(int64_t mtiles, int64_t Kp) {
 
 void dense_apply(const DenseOperator &op, const double2 *x, double2 *y, int R,
                  DevBuf<float2> &xs, hipStream_t s, const TuneEntry *forced) {
-    if (op.fp64) {   // complex128 operator: one pass per vector
-        Timer tm("dense_gemv_fp64", s);
-        for (int r = 0; r < R; r++) {
-            hipLaunchKernelGGL(dense_gemv64_kernel,
-                               dim3((unsigned)((op.n2 + 4 * G64_RW - 1) / (4 * G64_RW))),
-                               dim3(256), 0, s, op.B64.p, op.n2, x + r * op.n2, y + r * op.n2);
-            BEM_LAUNCH_CHECK();
+    if (op.fp64) {
+        for (int r0 = 0; r0 < R;) {
+            const int nr = mx_group(R - r0);
+            const double2 *xr = x + r0 * op.n2;
+            double2 *yr = y + r0 * op.n2;
+            if (nr >= 2) {
+                mx_apply((const double *)op.B64.p, op.n2, xr, yr, nr, xs, s);
+            } else {
+                Timer tm("dense_gemv_fp64", s);
+                hipLaunchKernelGGL(dense_gemv64_kernel,
+                                   dim3((unsigned)((op.n2 + 4 * G64_RW - 1) / (4 * G64_RW))), dim3(256),
+                                   0, s, op.B64.p, op.n2, xr, yr);
+                BEM_LAUNCH_CHECK();
+            }
+            r0 += nr;
         }
         return;
     }
     const TuneEntry te = forced ? *forced : tune_lookup(op.T, R);
     if (R >= te.gemm_min) dense_gemm(op, x, y, R, s);
-    else dense_gemv(op, x, y, R, xs, s, R >= te.skinny_min);
+    else dense_gemv(op, x, y, R, xs, s);
 }
 
 void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hipStream_t s) {

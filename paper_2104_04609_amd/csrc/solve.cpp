@@ -462,6 +462,8 @@ int64_t solve_footprint(bem_mesh *m, double2 k0, double2 k1, double rho,
     if (o.path == 1) b += dense_path_need(m, o);
     if (o.path == 3) b += hmat_bytes_estimate(m, k0, k1, rho);
     if (dense) b += 2 * G * n2 * 8 + dense_gemm_scratch_bytes(m, G);
+    if (o.path == 1)   // scratch of the assembled products
+        b += std::max(dense_mx_scratch_bytes(m->N, G, true), dense_mx_scratch_bytes(m->N, G, false));
     b += ((int64_t)n_waves + 8 * (int64_t)G) * n2 * c16;      // f, B, X, R, D, T, yw, vin, vout
     if (o.formulation == BEM_FORM_CALDERON) {
         b += 2 * (int64_t)G * n2 * c16;                       // t1, t2

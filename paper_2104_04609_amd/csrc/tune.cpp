@@ -206,21 +206,17 @@ TuneEntry autotune(bem_mesh *m, double2 k0, double2 k1, double rho, int R, int e
         best.t_asm = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         DevBuf<float2> xs;
         TuneEntry c = best;
-        c.gemm_min = R + 1;   // multi-vector GEMV
-        c.skinny_min = R + 1;
-        const double t_gemv = time_best([&] { dense_apply(*op, X.p, Y.p, R, xs, s, &c); }, s);
-        double t_skinny = 1e300, t_gemm = 1e300;
+        c.gemm_min = R + 1;   // up to 32 vectors per pass
+        const double t_small = time_best([&] { dense_apply(*op, X.p, Y.p, R, xs, s, &c); }, s);
+        double t_gemm = 1e300;
         if (R >= 2) {
-            c.skinny_min = 2;   // skinny MFMA product
-            t_skinny = time_best([&] { dense_apply(*op, X.p, Y.p, R, xs, s, &c); }, s);
-            c.gemm_min = R;     // MFMA GEMM
+            c.gemm_min = R;   // MFMA GEMM
             t_gemm = time_best([&] { dense_apply(*op, X.p, Y.p, R, xs, s, &c); }, s);
         }
-        // the whole bucket [b, 2b) takes the faster product
+        // the bucket [b, 2b) takes the faster product (the open one at most from
+        // the count timed)
         const int b = tune_bucket(R);
-        const double t_small = std::min(t_gemv, t_skinny);
-        best.gemm_min = t_gemm < t_small ? b : 2 * b;
-        best.skinny_min = t_skinny < t_gemv ? std::max(2, b) : 2 * b;
+        best.gemm_min = t_gemm < t_small ? std::max(b, std::min(R, 33)) : std::max(2 * b, b < 16 ? 0 : 33);
         best.t_dense = std::min(t_small, t_gemm);
         const double E = std::max(1, expected);
         best.path = best.t_asm + E * best.t_dense < E * best.t_mf ? 1 : 0;
