@@ -110,6 +110,7 @@ void mesh_trim(bem_mesh *m) {
     m->trirows.release();
     m->sym_items.release();
     m->sym_plan_id = nullptr;
+    m->field_work->release();
     m->parts.clear();
     m->part_vidx.clear();
 }
@@ -120,7 +121,7 @@ int64_t bem_mesh::device_bytes() const {
                 star_ptr.bytes() + star_idx.bytes() + near_pairs.bytes() + nf_rowptr.bytes() +
                 nf_col.bytes() + nf_cptr.bytes() + nf_contrib.bytes() + ss_tab.bytes() +
                 dyn64.bytes() + dyn32.bytes() + partial.bytes() + trirows.bytes() +
-                sym_items.bytes() + P_d.bytes();
+                sym_items.bytes() + field_work->bytes();
     for (const auto &kv : near_cache) b += kv.second->vals.bytes();
     for (const auto &kv : dense_cache) b += kv.second->bytes();
     for (const auto &kv : dense64_cache) b += kv.second->bytes();

@@ -247,6 +247,7 @@ struct bem_mesh {
     double centre[3] = {0, 0, 0};
     double diameter = 0;            // bounding-box diagonal
     std::vector<double> obj_radius; // circumradius about each object's centroid
+    std::vector<double> obj_box;    // [nobj][6] bounding box: lower, upper corner
 
     // device geometry
     bem::DevBuf<double> geo64;      // [T][GEO_STRIDE]
@@ -256,7 +257,27 @@ struct bem_mesh {
     bem::DevBuf<int32_t> tri_d;     // [T][3]
     bem::DevBuf<int32_t> star_ptr;  // [N+1] vertex -> (tri*3 + a), ascending
     bem::DevBuf<int32_t> star_idx;
-    bem::DevBuf<double> P_d;        // [N][3] vertices (field evaluation; on first use)
+    // workspace of the field evaluation, kept between calls; one call at a time
+    // holds it (until its kernels have finished), a concurrent one its own
+    struct FieldWork {
+        std::mutex mu;
+        bool have_P = false;
+        bem::DevBuf<double> P;        // [N][3] vertices
+        bem::DevBuf<double> tab;      // materials and boxes of the objects
+        bem::DevBuf<double> src, part;
+        bem::DevBuf<int32_t> list, region;
+        void release() {
+            std::lock_guard<std::mutex> g(mu);
+            have_P = false;
+            for (auto *b : {&P, &tab, &src, &part}) b->release();
+            list.release();
+            region.release();
+        }
+        int64_t bytes() const {
+            return P.bytes() + tab.bytes() + src.bytes() + part.bytes() + list.bytes() + region.bytes();
+        }
+    };
+    std::unique_ptr<FieldWork> field_work = std::make_unique<FieldWork>();
 
     // near field: ordered pairs (tau, sigma) sharing >= 1 vertex
     int64_t n_near = 0;

@@ -20,12 +20,16 @@
 // relative to p (Van Oosterom and Strackee, 1983):
 //   tan(Omega / 2) = a.(b x c) / (|a||b||c| + (a.b)|c| + (a.c)|b| + (b.c)|a|).
 // With disjoint objects one pass gives both the total solid angle and, from
-// the object-weighted sum, the object that encloses the point.  All sums are
+// the object-weighted sum, the object that encloses the point; points outside
+// every object's bounding box need none.  All sums are
 // accumulated in a fixed order (split partials added in split order).
 #include <algorithm>
 #include <cmath>
+#include <map>
+#include <mutex>
 
 #include "bem_internal.h"
+#include "fp64_math.h"
 
 namespace bem {
 
@@ -44,31 +48,6 @@ __device__ inline double qb(int i, int a) {
 constexpr double INV4PI = 0.079577471545947667884441881686257;
 constexpr double TWO_PI = 6.283185307179586476925286766559;
 constexpr double INV2PI = 0.15915494309189533576888376337251;
-
-// sin and cos of 2 pi t from a table of e^{2 pi i n / 256} (n = nearest
-// integer to 256 t) and the Taylor series of the remainder 2 pi f, |f| <=
-// 1/512 (terms beyond x^6 below 4e-18), joined by one complex product
-__device__ __forceinline__ void sincos_turns(double t, double &s, double &c,
-                                             const double2 *__restrict__ tab) {
-    const double n = __builtin_rint(256.0 * t);
-    const double x = __builtin_fma(-0.00390625, n, t) * TWO_PI;
-    const double x2 = x * x;
-    const double sn = __builtin_fma(__builtin_fma(x2, 1.0 / 120.0, -1.0 / 6.0), x2, 1.0) * x;
-    const double cs =
-        __builtin_fma(__builtin_fma(__builtin_fma(x2, -1.0 / 720.0, 1.0 / 24.0), x2, -0.5), x2, 1.0);
-    const double2 e = tab[((int64_t)n) & 255];
-    c = __builtin_fma(e.x, cs, -e.y * sn);
-    s = __builtin_fma(e.y, cs, e.x * sn);
-}
-
-// 1/sqrt(x): hardware estimate and two Newton steps
-__device__ __forceinline__ double rsq64(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = y * __builtin_fma(-h * y, y, 1.5);
-    y = y * __builtin_fma(-h * y, y, 1.5);
-    return y;
-}
 
 // per triangle: the 6 rule points, w |sigma| psi_h and w |sigma| phi_h there
 constexpr int SRC_STRIDE = 42;   // [0,18) points, [18,30) s_psi, [30,42) s_phi
@@ -110,89 +89,163 @@ __global__ __launch_bounds__(256) void field_sources_kernel(
     }
 }
 
-constexpr int WS = 10;   // winding tile doubles per triangle: 3 vertices, object
+// ------------------------------------------------------------------ regions
+// A point outside the bounding box of every object is outside all of them; the
+// others are listed (in any order: their regions do not depend on each other) and
+// their solid angles summed over ranges of the triangles.
+constexpr int WS = 10;          // winding tile doubles per triangle: 3 vertices, object
+constexpr int64_t FIELD_POINTS = 1 << 22;   // points per pass (bounds the workspace)
+constexpr int WIND_GROUPS = 2048;   // workgroups of the solid-angle sums
 
-// Work split over trial-triangle ranges (blockIdx.y): each (split, point)
-// writes its partial sums; the reduction kernels add the splits in order.
+__global__ __launch_bounds__(64) void count_zero_kernel(int32_t *count) { *count = 0; }
 
-// partial solid angles of all triangles of the split at each point:
-// [0] sum Omega_t, [1] sum Omega_t (object_t + 1)
+__global__ __launch_bounds__(256) void region_box_kernel(const double *__restrict__ pts, int64_t n,
+                                                         const double *__restrict__ box, int nobj,
+                                                         int32_t *__restrict__ region,
+                                                         int32_t *__restrict__ list,
+                                                         int32_t *__restrict__ count) {
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= n) return;
+    const double x = pts[3 * p], y = pts[3 * p + 1], z = pts[3 * p + 2];
+    bool in = false;
+    for (int o = 0; o < nobj; o++) {
+        const double *b = box + 6 * o;
+        in = in || (x >= b[0] && y >= b[1] && z >= b[2] && x <= b[3] && y <= b[4] && z <= b[5]);
+    }
+    region[p] = 0;
+    if (in) list[atomicAdd(count, 1)] = (int32_t)p;
+}
+
+// Triangle ranges for `count` listed points (the same for every kernel): about
+// WIND_GROUPS workgroups in all.
+__device__ __forceinline__ int wind_splits(int count, int max_split) {
+    const int pb = (count + 255) / 256;
+    return pb == 0 ? 0 : min(max_split, max(1, WIND_GROUPS / pb));
+}
+
+// Solid angles of the triangles of a range at the listed points:
+// [0] sum Omega_t, [1] sum Omega_t (object_t + 1).  Omega_t / 2 is the argument of
+// den + i num, so a sum of arguments is the argument of a product plus 2 pi for
+// every time the product passes the negative real axis: one atan2 per range and
+// object (and per change of object) instead of one per triangle, and 1/sqrt for
+// the three norms (1.33 ms for 10 201 points and 20 480 triangles with sqrt and
+// atan2 each, all points).
 __global__ __launch_bounds__(256) void winding_kernel(
     const double *__restrict__ P, const int32_t *__restrict__ tri,
-    const int32_t *__restrict__ tobj, int T, int split_len, const double *__restrict__ pts,
-    int64_t n, double *__restrict__ part) {
+    const int32_t *__restrict__ tobj, int T, const double *__restrict__ pts,
+    const int32_t *__restrict__ list, const int32_t *__restrict__ countp, int max_split,
+    double *__restrict__ part) {
     __shared__ double tile[FT * WS];
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t pp = p < n ? p : 0;
-    const double px = pts[3 * pp], py = pts[3 * pp + 1], pz = pts[3 * pp + 2];
-    const int t0 = blockIdx.y * split_len, t1 = min(T, t0 + split_len);
-    double om = 0.0, ow = 0.0;
-    for (int base = t0; base < t1; base += FT) {
-        const int cnt = min(FT, t1 - base);
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < cnt * WS; idx += blockDim.x) {
-            const int sl = idx / WS, f = idx - sl * WS;
-            const int64_t t = base + sl;
-            tile[idx] = f < 9 ? P[3 * tri[3 * t + f / 3] + f % 3] : (double)(tobj[t] + 1);
-        }
-        __syncthreads();
-        for (int sl = 0; sl < cnt; sl++) {
-            const double *v = tile + sl * WS;
-            const double a0 = v[0] - px, a1 = v[1] - py, a2 = v[2] - pz;
-            const double b0 = v[3] - px, b1 = v[4] - py, b2 = v[5] - pz;
-            const double c0 = v[6] - px, c1 = v[7] - py, c2 = v[8] - pz;
-            const double la = sqrt(a0 * a0 + a1 * a1 + a2 * a2);
-            const double lb = sqrt(b0 * b0 + b1 * b1 + b2 * b2);
-            const double lc = sqrt(c0 * c0 + c1 * c1 + c2 * c2);
-            const double num = a0 * (b1 * c2 - b2 * c1) + a1 * (b2 * c0 - b0 * c2) +
-                               a2 * (b0 * c1 - b1 * c0);
-            const double den = la * lb * lc + (a0 * b0 + a1 * b1 + a2 * b2) * lc +
-                               (a0 * c0 + a1 * c1 + a2 * c2) * lb +
-                               (b0 * c0 + b1 * c1 + b2 * c2) * la;
-            const double o = 2.0 * atan2(num, den);
+    const int count = *countp, nsplit = wind_splits(count, max_split);
+    const int pb = (count + 255) / 256, len = nsplit > 0 ? (T + nsplit - 1) / nsplit : 0;
+    // unit: 256 listed points and one range (uniform over the workgroup)
+    for (int unit = blockIdx.x; unit < pb * nsplit; unit += gridDim.x) {
+        const int split = unit / pb, idx0 = (unit - split * pb) * 256 + threadIdx.x;
+        const int64_t pp = list[min(idx0, count - 1)];
+        const double px = pts[3 * pp], py = pts[3 * pp + 1], pz = pts[3 * pp + 2];
+        const int t0 = split * len, t1 = min(T, t0 + len);
+        double om = 0.0, ow = 0.0, zr = 1.0, zi = 0.0;
+        int turns = 0, obj = -1;
+        auto close = [&]() {   // the product's argument into the sums
+            const double o = 2.0 * (atan2(zi, zr) + TWO_PI * turns);
             om += o;
-            ow += o * v[9];
+            ow += o * (obj + 1);
+            zr = 1.0;
+            zi = 0.0;
+            turns = 0;
+        };
+        for (int base = t0; base < t1; base += FT) {
+            const int cnt = min(FT, t1 - base);
+            __syncthreads();
+            for (int idx = threadIdx.x; idx < cnt * WS; idx += 256) {
+                const int sl = idx / WS, f = idx - sl * WS;
+                const int64_t t = base + sl;
+                tile[idx] = f < 9 ? P[3 * tri[3 * t + f / 3] + f % 3] : (double)tobj[t];
+            }
+            __syncthreads();
+            for (int sl = 0; sl < cnt; sl++) {
+                const double *v = tile + sl * WS;
+                if ((int)v[9] != obj) {   // uniform
+                    if (obj >= 0) close();
+                    obj = (int)v[9];
+                }
+                const double a0 = v[0] - px, a1 = v[1] - py, a2 = v[2] - pz;
+                const double b0 = v[3] - px, b1 = v[4] - py, b2 = v[5] - pz;
+                const double c0 = v[6] - px, c1 = v[7] - py, c2 = v[8] - pz;
+                const double aa = a0 * a0 + a1 * a1 + a2 * a2, bb = b0 * b0 + b1 * b1 + b2 * b2,
+                             cc = c0 * c0 + c1 * c1 + c2 * c2;
+                // (a point at a vertex: the norm is 0, as is its product)
+                const double ra = aa > 0 ? rsqrt64(aa) : 0.0, rb = bb > 0 ? rsqrt64(bb) : 0.0,
+                             rc = cc > 0 ? rsqrt64(cc) : 0.0;
+                const double la = aa * ra, lb = bb * rb, lc = cc * rc;
+                const double num = a0 * (b1 * c2 - b2 * c1) + a1 * (b2 * c0 - b0 * c2) +
+                                   a2 * (b0 * c1 - b1 * c0);
+                const double den = la * lb * lc + (a0 * b0 + a1 * b1 + a2 * b2) * lc +
+                                   (a0 * c0 + a1 * c1 + a2 * c2) * lb +
+                                   (b0 * c0 + b1 * c1 + b2 * c2) * la;
+                // over 4 |a||b||c|: the modulus is at most 1, near 1 for small triangles
+                const double sc = 0.25 * ra * rb * rc;
+                const double nr = den * sc, ni = num * sc;
+                const double wr = zr * nr - zi * ni, wi = zr * ni + zi * nr;
+                // arguments lie in (-pi, pi]: past pi, or past -pi
+                if (zi >= 0 && ni > 0 && wi < 0) turns++;
+                if (zi < 0 && ni < 0 && wi >= 0) turns--;
+                zr = wr;
+                zi = wi;
+            }
+            // keep the product's size (its argument stays)
+            const double big = fmax(fabs(zr), fabs(zi));
+            const double inv = big > 0 ? 1.0 / big : 1.0;
+            zr *= inv;
+            zi *= inv;
         }
-    }
-    if (p < n) {
-        part[2 * ((int64_t)blockIdx.y * n + p)] = om;
-        part[2 * ((int64_t)blockIdx.y * n + p) + 1] = ow;
+        if (obj >= 0) close();
+        if (idx0 < count) {
+            part[2 * ((int64_t)split * count + idx0)] = om;
+            part[2 * ((int64_t)split * count + idx0) + 1] = ow;
+        }
     }
 }
 
 // Closed disjoint surfaces: the total solid angle is 4 pi inside one object
 // and 0 outside all; inside object m the object-weighted sum is (m + 1) times
 // the total, since every other surface subtends 0.
-__global__ __launch_bounds__(256) void region_kernel(const double *__restrict__ part, int nsplit,
-                                                     int64_t n, int nobj,
-                                                     int32_t *__restrict__ region) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
+__global__ __launch_bounds__(256) void region_kernel(const double *__restrict__ part,
+                                                     const int32_t *__restrict__ list,
+                                                     const int32_t *__restrict__ countp, int max_split,
+                                                     int nobj, int32_t *__restrict__ region) {
+    const int count = *countp, nsplit = wind_splits(count, max_split);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= count) return;
     double om = 0.0, ow = 0.0;
+#pragma unroll 4
     for (int sp = 0; sp < nsplit; sp++) {
-        om += part[2 * ((int64_t)sp * n + p)];
-        ow += part[2 * ((int64_t)sp * n + p) + 1];
+        om += part[2 * ((int64_t)sp * count + i)];
+        ow += part[2 * ((int64_t)sp * count + i) + 1];
     }
     int r = 0;
     if (fabs(om) > TWO_PI) r = min(nobj, max(1, (int)lround(ow / om)));
-    region[p] = r;
+    region[list[i]] = r;
 }
 
+// ------------------------------------------------------------------- layers
 // partial single- and double-layer sums of the split's triangles at each
-// point, with the wavenumber and the triangles of the point's region
-// Three waves per SIMD (measured against two: 5 % faster; four: 2.6x slower).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void field_kernel(
+// point, with the wavenumber and the triangles of the point's region.  Bound by
+// FP64 VALU issue: about 50 instructions per (point, trial point) with the
+// functions of fp64_math.h and F = (i k E - G) / r^2; the complex variant (LOSSY)
+// is a kernel of its own, a branch per pair otherwise (96 instructions, 3.20 ms for
+// 10 201 points and 20 480 triangles).
+template <bool LOSSY>
+__global__ __launch_bounds__(256) void field_kernel(
     const double *__restrict__ src, const double *__restrict__ geo,
     const int32_t *__restrict__ tobj, int T, int split_len, const double *__restrict__ pts,
     const int32_t *__restrict__ region, int64_t n, double2 k0, const double *__restrict__ omat,
     double *__restrict__ part) {
     __shared__ double tile[FT * FS];
-    __shared__ double2 etab[256];   // e^{2 pi i n / 256}
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) {
-        double sn, cs;
-        sincos(i * (TWO_PI / 256.0), &sn, &cs);
-        etab[i] = make_double2(cs, sn);
-    }
+    __shared__ double2 etab[256];
+    __shared__ double xtab[DECAY_TAB];
+    phase_table(etab);
+    if (LOSSY) decay_table(xtab);
     // (the first tile's barrier orders these writes before any read)
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t pp = p < n ? p : 0;
@@ -201,7 +254,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     const bool ext = reg == 0;
     // interior material of the enclosing object: omat[object] = (Re k, Im k, rho)
     const double2 k = ext ? k0 : make_double2(omat[3 * (reg - 1)], omat[3 * (reg - 1) + 1]);
-    const double krev = k.x * INV2PI;
+    const double krev = k.x * (INV2PI * PHASE64);
+    const double kdec = -k.y * 1.4426950408889634073599246810019;   // log2 of the decay
     const int t0 = blockIdx.y * split_len, t1 = min(T, t0 + split_len);
     double sr = 0, si = 0, dr = 0, di = 0;
     for (int base = t0; base < t1; base += FT) {
@@ -225,28 +279,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
             const double dn = s[SRC_STRIDE + 3] -
                               (px * s[SRC_STRIDE] + py * s[SRC_STRIDE + 1] + pz * s[SRC_STRIDE + 2]);
             double fr = 0, fi = 0;
+#pragma unroll
             for (int q = 0; q < 6; q++) {
                 const double ex = s[3 * q] - px, ey = s[3 * q + 1] - py, ez = s[3 * q + 2] - pz;
                 const double r2 = ex * ex + ey * ey + ez * ez;
-                const double ri = rsq64(r2);
+                const double ri = rsqrt64(r2);
                 const double r = r2 * ri;
-                double sn, cs;
-                sincos_turns(krev * r, sn, cs, etab);
-                const double mag = (k.y != 0.0 ? exp(-k.y * r) : 1.0) * ri;
-                const double Gr = cs * mag, Gi = sn * mag;     // 4 pi G
-                // 4 pi G (i k r - 1) / r^2
-                const double tr = -1.0 - k.y * r, ti = k.x * r;
-                const double ri2 = ri * ri;   // (= 1 / r2)
-                const double Fr = (Gr * tr - Gi * ti) * ri2, Fi = (Gr * ti + Gi * tr) * ri2;
+                double Er, Ei;
+                sincos_256(krev * r, Ei, Er, etab);
+                if (LOSSY) {
+                    const double d = decay64(kdec * r, xtab);
+                    Er *= d;
+                    Ei *= d;
+                }
+                const double Gr = Er * ri, Gi = Ei * ri;     // 4 pi G
+                // 4 pi G (i k r - 1) / r^2 = (i k E - G) / r^2
+                double Fr = __builtin_fma(-k.x, Ei, -Gr), Fi = __builtin_fma(k.x, Er, -Gi);
+                if (LOSSY) {
+                    Fr = __builtin_fma(-k.y, Er, Fr);
+                    Fi = __builtin_fma(-k.y, Ei, Fi);
+                }
+                const double ri2 = ri * ri;
+                Fr *= ri2;
+                Fi *= ri2;
                 const double ar = s[18 + 2 * q], ai = s[18 + 2 * q + 1];
                 const double br = s[30 + 2 * q], bi = s[30 + 2 * q + 1];
-                sr += Gr * ar - Gi * ai;
-                si += Gr * ai + Gi * ar;
-                fr += Fr * br - Fi * bi;
-                fi += Fr * bi + Fi * br;
+                sr = __builtin_fma(Gr, ar, __builtin_fma(-Gi, ai, sr));
+                si = __builtin_fma(Gr, ai, __builtin_fma(Gi, ar, si));
+                fr = __builtin_fma(Fr, br, __builtin_fma(-Fi, bi, fr));
+                fi = __builtin_fma(Fr, bi, __builtin_fma(Fi, br, fi));
             }
-            dr += dn * fr;
-            di += dn * fi;
+            dr = __builtin_fma(dn, fr, dr);
+            di = __builtin_fma(dn, fi, di);
         }
     }
     if (p < n) {
@@ -266,6 +330,7 @@ __global__ __launch_bounds__(256) void field_reduce_kernel(
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     double sr = 0, si = 0, dr = 0, di = 0;
+#pragma unroll 4
     for (int sp = 0; sp < nsplit; sp++) {
         const double *o = part + 4 * ((int64_t)sp * n + p);
         sr += o[0];
@@ -290,58 +355,121 @@ __global__ __launch_bounds__(256) void field_reduce_kernel(
     out[p] = make_double2(ur, ui);
 }
 
+// Triangle ranges of the layer sums: the number of equal workgroups that fills
+// whole rounds of resident ones best.
+int field_splits(int T, int64_t pb, const void *kern) {
+    static std::mutex mu;
+    static std::map<std::pair<int, const void *>, int> cache;
+    int dev = 0, slots = 0;
+    BEM_HIP(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> g(mu);
+        int &c = cache[{dev, kern}];
+        if (c == 0) {
+            int cus = 0, per = 0;
+            BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+            BEM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, 256, 0));
+            c = std::max(1, cus * per);
+        }
+        slots = c;
+    }
+    int best = 1;
+    double best_cost = 1e300;
+    for (int ns = 1; ns <= 256 && (ns == 1 || ns * FT / 2 <= T); ns++) {
+        const int len = (T + ns - 1) / ns;
+        // + tables and the first tile, in triangles; half a round of a launch of many
+        const double waves = (double)pb * ns / slots;
+        const double cost = (waves <= 4 ? std::ceil(waves) : waves + 0.5) * (len + 8.0);
+        if (cost < best_cost * (1 - 1e-9)) {
+            best_cost = cost;
+            best = ns;
+        }
+    }
+    return best;
+}
+
 }   // namespace
 
 void field_eval(bem_mesh *m, double2 k0, double2 k1, double rho, const double *dir,
                 const double2 *x, const double *pts, int64_t n, double2 *out, int32_t *region,
                 hipStream_t s, const ObjMaterials *om) {
     if (n == 0) return;
-    const int T = (int)m->T;
-    if (!m->P_d.p) m->P_d.upload(m->P);
-    std::vector<double> mat(3 * (size_t)m->nobj);
-    for (int o = 0; o < m->nobj; o++) {
+    const int T = (int)m->T, nobj = m->nobj;
+    // the mesh's workspace when no other call holds it, else an own one (released
+    // or free again once the stream has been waited for, below)
+    bem_mesh::FieldWork own, &mw = *m->field_work;
+    std::unique_lock<std::mutex> lk(mw.mu, std::try_to_lock);
+    bem_mesh::FieldWork &w = lk.owns_lock() ? mw : own;
+    auto grow = [](auto &b, size_t need) {
+        if (b.n < need) b.alloc(need);
+    };
+    // per object: material (Re k, Im k, rho), then bounding box
+    std::vector<double> tab(9 * (size_t)nobj);
+    bool lossy = k0.y != 0.0;
+    for (int o = 0; o < nobj; o++) {
         const double2 ko = om ? om->k[o] : k1;
-        mat[3 * o] = ko.x;
-        mat[3 * o + 1] = ko.y;
-        mat[3 * o + 2] = om ? om->rho[o] : rho;
+        tab[3 * o] = ko.x;
+        tab[3 * o + 1] = ko.y;
+        tab[3 * o + 2] = om ? om->rho[o] : rho;
+        lossy = lossy || ko.y != 0.0;
     }
-    DevBuf<double> matd;
-    matd.upload(mat);
-    const unsigned pb = (unsigned)((n + 255) / 256);
-    // enough workgroups to fill the device (about 2048), splits of >= 4 tiles
-    const int max_split = std::max(1, T / (4 * FT));
-    const int nsplit = (int)std::min<int64_t>(max_split, std::max<int64_t>(1, (2048 + pb - 1) / pb));
+    std::copy(m->obj_box.begin(), m->obj_box.end(), tab.begin() + 3 * nobj);
+    w.tab.upload(tab);
+    grow(w.P, (size_t)(3 * m->N));
+    if (!w.have_P) {
+        BEM_HIP(hipMemcpy(w.P.p, m->P.data(), m->P.size() * sizeof(double), hipMemcpyHostToDevice));
+        w.have_P = true;
+    }
+    const double *omat = w.tab.p, *box = w.tab.p + 3 * nobj;
+    const int64_t all = n;
+    n = std::min(n, FIELD_POINTS);
+    unsigned pb = (unsigned)((n + 255) / 256);
+    const auto layers = lossy ? field_kernel<true> : field_kernel<false>;
+    const int nsplit = field_splits(T, pb, (const void *)layers);
     const int split_len = (T + nsplit - 1) / nsplit;
-    DevBuf<double> src((size_t)SRC_STRIDE * T);
-    DevBuf<double> part((size_t)nsplit * n * 4);
-    DevBuf<int32_t> reg_own;
-    int32_t *reg = region;
+    // solid angles: at most WIND_GROUPS workgroups' points and ranges, or one range
+    const int max_split = std::max(1, T / FT);
+    grow(w.src, (size_t)SRC_STRIDE * T);
+    grow(w.part, std::max((size_t)nsplit * n * 4,
+                          2 * std::max((size_t)n, (size_t)256 * WIND_GROUPS) + 512));
+    grow(w.list, (size_t)n + 1);
+    int32_t *reg = region, *count = w.list.p, *list = w.list.p + 1;
     if (!reg) {
-        reg_own.alloc((size_t)n);
-        reg = reg_own.p;
+        grow(w.region, (size_t)n);
+        reg = w.region.p;
     }
-    hipLaunchKernelGGL(field_sources_kernel, dim3((T + 255) / 256), dim3(256), 0, s, m->P_d.p,
-                       m->tri_d.p, m->tst.p, x, m->N, T, src.p);
+    hipLaunchKernelGGL(field_sources_kernel, dim3((T + 255) / 256), dim3(256), 0, s, w.P.p, m->tri_d.p,
+                       m->tst.p, x, m->N, T, w.src.p);
     BEM_LAUNCH_CHECK();
-    {
-        Timer tm("field_winding", s);
-        hipLaunchKernelGGL(winding_kernel, dim3(pb, (unsigned)nsplit), dim3(256), 0, s, m->P_d.p,
-                           m->tri_d.p, m->tobj_d.p, T, split_len, pts, n, part.p);
+    for (int64_t p0 = 0; p0 < all; p0 += FIELD_POINTS, pts += 3 * n, out += n) {
+        n = std::min(all - p0, FIELD_POINTS);
+        pb = (unsigned)((n + 255) / 256);
+        if (region) reg = region + p0;
+        {
+            Timer tm("field_winding", s);
+            hipLaunchKernelGGL(count_zero_kernel, dim3(1), dim3(1), 0, s, count);
+            BEM_LAUNCH_CHECK();
+            hipLaunchKernelGGL(region_box_kernel, dim3(pb), dim3(256), 0, s, pts, n, box, nobj, reg, list,
+                               count);
+            BEM_LAUNCH_CHECK();
+            hipLaunchKernelGGL(winding_kernel, dim3(WIND_GROUPS), dim3(256), 0, s, w.P.p, m->tri_d.p,
+                               m->tobj_d.p, T, pts, list, count, max_split, w.part.p);
+            BEM_LAUNCH_CHECK();
+            hipLaunchKernelGGL(region_kernel, dim3(pb), dim3(256), 0, s, w.part.p, list, count, max_split,
+                               nobj, reg);
+            BEM_LAUNCH_CHECK();
+        }
+        {
+            Timer tm("field_eval", s);
+            hipLaunchKernelGGL(layers, dim3(pb, (unsigned)nsplit), dim3(256), 0, s, w.src.p, m->geo64.p,
+                               m->tobj_d.p, T, split_len, pts, reg, n, k0, omat, w.part.p);
+            BEM_LAUNCH_CHECK();
+        }
+        hipLaunchKernelGGL(field_reduce_kernel, dim3(pb), dim3(256), 0, s, w.part.p, nsplit, pts, reg, n, k0,
+                           omat, dir[0], dir[1], dir[2], out);
         BEM_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(region_kernel, dim3(pb), dim3(256), 0, s, part.p, nsplit, n, m->nobj, reg);
-    BEM_LAUNCH_CHECK();
-    {
-        Timer tm("field_eval", s);
-        hipLaunchKernelGGL(field_kernel, dim3(pb, (unsigned)nsplit), dim3(256), 0, s, src.p,
-                           m->geo64.p, m->tobj_d.p, T, split_len, pts, reg, n, k0, matd.p,
-                           part.p);
-        BEM_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(field_reduce_kernel, dim3(pb), dim3(256), 0, s, part.p, nsplit, pts, reg, n,
-                       k0, matd.p, dir[0], dir[1], dir[2], out);
-    BEM_LAUNCH_CHECK();
-    BEM_HIP(hipStreamSynchronize(s));   // src, part and the own region buffer are released on return
+    BEM_HIP(hipStreamSynchronize(s));   // the workspace is free again
 }
 
 }   // namespace bem

@@ -154,6 +154,15 @@ void mesh_build(bem_mesh *m, const double *P, int64_t N, const int32_t *tri,
             }
         m->obj_radius[o] = r;
     }
+    m->obj_box.assign(6 * (size_t)nobj, 1e300);
+    for (int o = 0; o < nobj; o++) std::fill_n(m->obj_box.begin() + 6 * o + 3, 3, -1e300);
+    for (int64_t v = 0; v < N; v++) {
+        double *b = &m->obj_box[6 * (size_t)m->vobj[v]];
+        for (int c = 0; c < 3; c++) {
+            b[c] = std::min(b[c], P[3 * v + c]);
+            b[3 + c] = std::max(b[3 + c], P[3 * v + c]);
+        }
+    }
 
     // device geometry records
     const Rules &R = rules();
