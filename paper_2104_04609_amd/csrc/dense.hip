@@ -441,41 +441,30 @@ __global__ __launch_bounds__(256) void dense_gemv1_kernel(const float2 *__restri
 // ------------------------------------------------ multi-RHS product on MFMA
 // Y = B X for n_rhs right-hand sides as one real FP32 GEMM: B is read as a
 // real [M][Kp] matrix (M = 2N rows, Kp = 4N: re/im interleaved), X as the
-// real [Kp][Np] matrix with rows 2k = (Re X_k, Im X_k) and 2k+1 =
-// (-Im X_k, Re X_k) per right-hand side (columns 2r, 2r+1), so that columns
-// 2r and 2r+1 of the product are Re and Im of column r of B X.
+// transposed real columns XT[Np][Kp] of mx_prep_kernel (2r: Re, -Im; 2r + 1: Im,
+// Re interleaved), so that columns 2r and 2r+1 of the product are Re and Im of
+// column r of B X.
 constexpr int GM = 128, GN = 128, GK = 32;   // block tile and K step
 constexpr int GKC = 4096;                    // largest split-K chunk (FP32 MFMA accumulation)
-constexpr int GKC_MIN = 1024;                // smallest split-K chunk
+constexpr int GLD = GK + 4;                  // padded rows: 16 lanes of a read in distinct banks
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// Xp[2k][2r], Xp[2k][2r+1], Xp[2k+1][2r], Xp[2k+1][2r+1] from x[r][k] (RHS-major)
-__global__ __launch_bounds__(256) void gemm_xprep_kernel(const double2 *__restrict__ x, int R,
-                                                         int64_t K, int Np,
-                                                         float *__restrict__ Xp) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= K * (Np / 2)) return;
-    const int64_t k = id / (Np / 2);
-    const int r = (int)(id - k * (Np / 2));
-    const double2 v = r < R ? x[(int64_t)r * K + k] : make_double2(0.0, 0.0);
-    float *row0 = Xp + (2 * k) * Np, *row1 = row0 + Np;
-    row0[2 * r] = (float)v.x;
-    row0[2 * r + 1] = (float)v.y;
-    row1[2 * r] = (float)(-v.y);
-    row1[2 * r + 1] = (float)v.x;
-}
-
 // partial products of K chunk blockIdx.z: Yp[z][M][Np]; 4 waves, 64 x 64 each.
-// The next K step's tiles are loaded into registers (16-byte loads) while the
-// current one is multiplied from LDS, then stored to the other LDS buffer:
-// one barrier per K step.  Kp and Np are multiples of 4, chunk ends of 32.
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(const float *__restrict__ A,
-                                                        const float *__restrict__ Xp,
-                                                        float *__restrict__ Yp, int64_t M,
-                                                        int64_t Kp, int Np, int kchunk) {
-    __shared__ float As[2][GM][GK + 1];
-    __shared__ float Bs[2][GK][GN];
+// Bound by the FP32 matrix cores.  The next K step's tiles are loaded into
+// registers (16-byte loads) while the current one is multiplied from LDS, then
+// stored to the other LDS buffer: one barrier per K step.  Both tiles are kept by
+// rows along K, and a lane reads four consecutive k of its row at once: the two
+// k-slots of v_mfma_f32_32x32x2 may hold any k as long as A and X agree, so
+// instruction e of a group of 8 takes k = 4 (lane / 32) + e.  Four reads per 16
+// matrix instructions, issued a group ahead (single values of both operands read
+// right before their use: 2.42 ms a product of 64 vectors at 10 242 vertices, 94
+// TFLOP/s in this kernel; now 1.88).  Kp is a multiple of 4, chunk ends of 32.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gemm_mfma_kernel(
+    const float *__restrict__ A, const float *__restrict__ XT, float *__restrict__ Yp, int64_t M,
+    int64_t Kp, int Np, int kchunk) {
+    __shared__ fvec4 As[2][GM * GLD / 4];
+    __shared__ fvec4 Bs[2][GN * GLD / 4];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t m0 = (int64_t)blockIdx.x * GM;
     const int n0 = blockIdx.y * GN;
@@ -489,59 +478,59 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const float *__restrict_
         for (int j = 0; j < 2; j++)
 #pragma unroll
             for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
-    // per thread: 4 float4 of the A tile (rows idx / 8, columns 4 (idx % 8)) and
-    // 4 float4 of the B tile (rows idx / 32, columns 4 (idx % 32)), idx = i 256 + t,
-    // held in named registers (no local array)
-    float4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
-    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-#define BEM_GEMM_LOAD_ONE(i, RA, RB)                                                            \
-    {                                                                                          \
-        const int idx = (i) * 256 + t;                                                         \
-        const int64_t gr = m0 + idx / 8, gc = k0 + 4 * (idx % 8);                              \
-        RA = (gr < M && gc < kend) ? *(const float4 *)(A + gr * Kp + gc) : zero4;              \
-        const int64_t br = k0 + idx / 32;                                                      \
-        RB = br < kend ? *(const float4 *)(Xp + br * Np + n0 + 4 * (idx % 32)) : zero4;        \
-    }
-#define BEM_GEMM_STORE_ONE(i, RA, RB)                                                           \
-    {                                                                                          \
-        const int idx = (i) * 256 + t;                                                         \
-        float *a = &As[buf][idx / 8][4 * (idx % 8)];                                           \
-        a[0] = RA.x;                                                                           \
-        a[1] = RA.y;                                                                           \
-        a[2] = RA.z;                                                                           \
-        a[3] = RA.w;                                                                           \
-        *(float4 *)&Bs[buf][idx / 32][4 * (idx % 32)] = RB;                                     \
-    }
+    // per thread: 4 float4 of either tile (rows i 32 + t / 8, columns 4 (t % 8))
+    const int tr = t >> 3, tc = t & 7;
+    const fvec4 zero4 = fvec4{0.f, 0.f, 0.f, 0.f};
+    fvec4 ra[4], rb[4];
     auto gload = [&](int64_t k0) {
-        BEM_GEMM_LOAD_ONE(0, ra0, rb0)
-        BEM_GEMM_LOAD_ONE(1, ra1, rb1)
-        BEM_GEMM_LOAD_ONE(2, ra2, rb2)
-        BEM_GEMM_LOAD_ONE(3, ra3, rb3)
+        const int64_t k = k0 + 4 * tc;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int64_t row = m0 + 32 * i + tr;
+            ra[i] = row < M && k < kend ? *(const fvec4 *)(A + row * Kp + k) : zero4;
+            rb[i] = k < kend ? *(const fvec4 *)(XT + (int64_t)(n0 + 32 * i + tr) * Kp + k) : zero4;
+        }
     };
     auto lstore = [&](int buf) {
-        BEM_GEMM_STORE_ONE(0, ra0, rb0)
-        BEM_GEMM_STORE_ONE(1, ra1, rb1)
-        BEM_GEMM_STORE_ONE(2, ra2, rb2)
-        BEM_GEMM_STORE_ONE(3, ra3, rb3)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            As[buf][(32 * i + tr) * (GLD / 4) + tc] = ra[i];
+            Bs[buf][(32 * i + tr) * (GLD / 4) + tc] = rb[i];
+        }
     };
-#undef BEM_GEMM_LOAD_ONE
-#undef BEM_GEMM_STORE_ONE
     gload(kbeg);
     lstore(0);
     __syncthreads();
     int cur = 0;
+    const int ra0 = (wr + (lane & 31)) * (GLD / 4) + (lane >> 5),
+              rb0 = (wc + (lane & 31)) * (GLD / 4) + (lane >> 5);
     for (int64_t k0 = kbeg; k0 < kend; k0 += GK) {
         const bool more = k0 + GK < kend;
         if (more) gload(k0 + GK);
+        fvec4 va[2][2], vb[2][2];   // [group parity][tile]
+        auto read = [&](int gp, int p) {
 #pragma unroll
-        for (int kk = 0; kk < GK; kk += 2) {
-            const int ka = kk + (lane >> 5);
-            const float a0 = As[cur][wr + (lane & 31)][ka], a1 = As[cur][wr + 32 + (lane & 31)][ka];
-            const float b0 = Bs[cur][ka][wc + (lane & 31)], b1 = Bs[cur][ka][wc + 32 + (lane & 31)];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
+            for (int i = 0; i < 2; i++) {
+                va[p][i] = As[cur][ra0 + 32 * i * (GLD / 4) + 2 * gp];
+                vb[p][i] = Bs[cur][rb0 + 32 * i * (GLD / 4) + 2 * gp];
+            }
+        };
+        read(0, 0);
+#pragma unroll
+        for (int gp = 0; gp < GK / 8; gp++) {
+            const int p = gp & 1;
+            if (gp + 1 < GK / 8) read(gp + 1, p ^ 1);
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[p][i][e], vb[p][j][e],
+                                                                         acc[i][j], 0, 0, 0);
+            // the next group's reads before this group's products
+            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
         }
         if (more) lstore(cur ^ 1);
         __syncthreads();
@@ -562,21 +551,32 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const float *__restrict_
             }
 }
 
-// y[r][m] = sum over K chunks (fixed order, FP64) of (Yp[.][m][2r], Yp[.][m][2r+1])
+// y[r][m] = sum over K chunks (fixed order, FP64) of (Yp[.][m][2r], Yp[.][m][2r+1]);
+// 32 rows and 32 vectors per workgroup, turned through LDS so that both the
+// partial products (by rows) and y (by vectors) are read and written along lines
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float *__restrict__ Yp,
                                                           int nchunks, int64_t M, int Np, int R,
                                                           double2 *__restrict__ y) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= M * R) return;
-    const int r = (int)(id / M);
-    const int64_t m = id - (int64_t)r * M;
-    double sr = 0.0, si = 0.0;
-    for (int c = 0; c < nchunks; c++) {
-        const float *row = Yp + ((int64_t)c * M + m) * Np;
-        sr += row[2 * r];
-        si += row[2 * r + 1];
+    __shared__ double2 tile[32][33];
+    const int64_t m0 = (int64_t)blockIdx.x * 32;
+    const int r0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    for (int q = ty; q < 32; q += 8) {
+        const int64_t m = m0 + q;
+        double2 v = make_double2(0.0, 0.0);
+        if (m < M && r0 + tx < R) {
+            const float2 *p = reinterpret_cast<const float2 *>(Yp) + m * (Np / 2) + r0 + tx;
+#pragma unroll 4
+            for (int c = 0; c < nchunks; c++) {
+                const float2 f = p[(int64_t)c * M * (Np / 2)];
+                v.x += f.x;
+                v.y += f.y;
+            }
+        }
+        tile[q][tx] = v;
     }
-    y[(int64_t)r * M + m] = make_double2(sr, si);
+    __syncthreads();
+    for (int q = ty; q < 32; q += 8)
+        if (m0 + tx < M && r0 + q < R) y[(int64_t)(r0 + q) * M + m0 + tx] = tile[tx][q];
 }
 
 // ----------------------------- up to 32 right-hand sides: skinny MFMA product
@@ -1091,17 +1091,24 @@ void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, De
     }
 }
 
+// smallest split-K chunk: at most about 40 partial products, none below 256 k
+static int gemm_kmin(int64_t Kp) {
+    return (int)std::min<int64_t>(1024, std::max<int64_t>(256, (Kp / 40 + GK - 1) / GK * GK));
+}
+
 int64_t dense_gemm_scratch_bytes(const bem_mesh *m, int R) {
     const int64_t M = 2 * m->N, Kp = 2 * M;
-    const int64_t Np = 2 * (((int64_t)R + 63) / 64) * 64, nchunks = (Kp + GKC_MIN - 1) / GKC_MIN;
+    const int64_t Np = 2 * (((int64_t)R + 63) / 64) * 64, kmin = gemm_kmin(Kp),
+                  nchunks = (Kp + kmin - 1) / kmin;
     return (Kp * Np + nchunks * M * Np) * (int64_t)sizeof(float);
 }
 
 namespace {
 
-// Split-K chunk of the MFMA product: the multiple of the K step between
-// GKC_MIN and GKC whose grid fills the resident workgroup slots most evenly
-// (whole waves of workgroups), longer chunks preferred at equal fill.
+// Split-K chunk of the MFMA product: all workgroups cost the same, so the chunk
+// (a multiple of the K step) that makes rounds of resident workgroups times its
+// length, with three steps for the first loads and the output, least; longer
+// chunks at equal cost.
 int gemm_kchunk(int64_t mtiles, int64_t Kp) {
     static int slots = 0;
     if (slots == 0) {
@@ -1112,13 +1119,12 @@ int gemm_kchunk(int64_t mtiles, int64_t Kp) {
         slots = std::max(1, cus * std::max(per, 1));
     }
     int best = GKC;
-    double best_fill = -1;
-    for (int kc = GKC; kc >= GKC_MIN; kc -= GK) {
+    double best_cost = 1e300;
+    for (int kc = GKC; kc >= gemm_kmin(Kp); kc -= GK) {
         const int64_t nch = (Kp + kc - 1) / kc;
-        const double waves = (double)(mtiles * nch) / slots;
-        const double fill = waves / std::ceil(waves);
-        if (fill > best_fill + 0.01) {
-            best_fill = fill;
+        const double cost = std::ceil((double)(mtiles * nch) / slots) * (std::min<int64_t>(kc, Kp) + 3 * GK);
+        if (cost < best_cost * (1 - 1e-9)) {
+            best_cost = cost;
             best = kc;
         }
     }
@@ -1175,9 +1181,8 @@ void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hi
         Xp = own_x.p;
         Yp = own_y.p;
     }
-    const int64_t prep = K * Rp;
-    hipLaunchKernelGGL(gemm_xprep_kernel, dim3((unsigned)((prep + 255) / 256)), dim3(256), 0, s, x,
-                       R, K, Np, Xp);
+    hipLaunchKernelGGL(mx_prep_kernel<float>, dim3((unsigned)((K + 255) / 256), Rp), dim3(256), 0, s, x, R,
+                       K, Xp);
     BEM_LAUNCH_CHECK();
     {
         Timer tm("dense_gemm_mfma", s);
@@ -1186,14 +1191,10 @@ void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hi
                            (const float *)op.B.p, Xp, Yp, M, Kp, Np, kchunk);
         BEM_LAUNCH_CHECK();
     }
-    const int64_t red = M * R;
-    hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((red + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((M + 31) / 32), (R + 31) / 32), dim3(256), 0, s,
                        Yp, nchunks, M, Np, R, y);
     BEM_LAUNCH_CHECK();
-    // the workspace is free again once these kernels have finished (an own
-    // one is freed on return, which waits for them as well)
-    if (lk.owns_lock()) BEM_HIP(hipStreamSynchronize(s));
-    BEM_HIP(hipStreamSynchronize(s));   // Xp, Yp are released on return
+    BEM_HIP(hipStreamSynchronize(s));   // the workspace is free again, or released
 }
 
 namespace {
