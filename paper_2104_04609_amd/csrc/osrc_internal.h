@@ -115,7 +115,7 @@ struct OsrcSymbolicState {
     std::vector<int32_t> gptr, gcol;
     std::vector<double> Mv, Sv;
     LdlSymbolic sym;
-    DevBuf<int32_t> gptr_d, gcol_d, perm_d, Rj_d, Li_d;
+    DevBuf<int32_t> gptr_d, gcol_d, perm_d, Rj_d, Li_d, Rmap_d;
     std::vector<int32_t> lbcount, lrcount;   // blocks and rows per level (host)
     std::vector<int32_t> lptr_h, lbptr_h;
     std::vector<int64_t> lext_f, lext_b;
@@ -162,6 +162,12 @@ struct TaskList {
     int nbase;
     int64_t in_stride, out_stride, work_stride;
 };
+
+// row-wise copies of L (lr[p] = lc[rmap[p]]) and the transposed block
+// inverses of nf factors from the column-wise L and the inverses
+void launch_ldl_mirror(int nf, int nblocks, const int4 *lblkd, int64_t nnz, int64_t nd,
+                       const int32_t *rmap, const double2 *lc, double2 *lr, const double2 *il,
+                       double2 *ilt, hipStream_t s);
 
 void launch_ldl_solve(const LdlDev &L, const LdlSplitDev &P, TaskList tasks, int ntasks,
                       int nrhs, hipStream_t s);

@@ -577,7 +577,36 @@ __global__ __launch_bounds__(256) void pade_pair_kernel(int n, int nrhs, PadeArg
     else pade_sum_row(i, y - nrhs, pb);
 }
 
+// Second layouts of a new set of factors: workgroup b < nblocks transposes the
+// dense inverse of block b, the later ones gather 256 entries of L each;
+// blockIdx.y is the factor.  Bound by the gather's reads.  Made here, half of
+// what the factors hold on the device is neither formed on the host nor sent.
+__global__ __launch_bounds__(256) void ldl_mirror_kernel(
+    int nblocks, const int4 *__restrict__ lblkd, int64_t nnz, int64_t nd,
+    const int32_t *__restrict__ rmap, const double2 *__restrict__ lc, double2 *__restrict__ lr,
+    const double2 *__restrict__ il, double2 *__restrict__ ilt) {
+    const int64_t f = blockIdx.y;
+    if ((int)blockIdx.x < nblocks) {
+        const int4 d = lblkd[blockIdx.x];
+        const int w = d.y;
+        const double2 *x = il + f * nd + d.z;
+        double2 *y = ilt + f * nd + d.z;
+        for (int e = threadIdx.x; e < w * w; e += 256) y[e] = x[(e % w) * w + e / w];
+        return;
+    }
+    const int64_t p = (int64_t)(blockIdx.x - nblocks) * 256 + threadIdx.x;
+    if (p < nnz) lr[f * nnz + p] = lc[f * nnz + rmap[p]];
+}
+
 }   // namespace
+
+void launch_ldl_mirror(int nf, int nblocks, const int4 *lblkd, int64_t nnz, int64_t nd,
+                       const int32_t *rmap, const double2 *lc, double2 *lr, const double2 *il,
+                       double2 *ilt, hipStream_t s) {
+    hipLaunchKernelGGL(ldl_mirror_kernel, dim3((unsigned)(nblocks + (nnz + 255) / 256), nf),
+                       dim3(256), 0, s, nblocks, lblkd, nnz, nd, rmap, lc, lr, il, ilt);
+    BEM_LAUNCH_CHECK();
+}
 
 int ldl_split_max_lds() {
     static const int lds = [] {

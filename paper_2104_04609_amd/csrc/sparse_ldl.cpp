@@ -230,44 +230,119 @@ LdlSymbolic ldl_symbolic(int n, const std::vector<int32_t> &ptr,
     return S;
 }
 
+namespace {
+
+typedef double cx2 __attribute__((vector_size(16)));   // (re, im)
+
+// w[row[p]] -= sum_c L_c[p] f_c over NC columns of one row list.  With L
+// times Re f and L times Im f summed apart, the two halves of a product are
+// exchanged once per row and not once per column: no test for NaN, no branch.
+template <int NC>
+inline void ldl_update(double *w, const int32_t *row, int n, const double *const *L,
+                       const double *fr, const double *fi) {
+    for (int p = 0; p < n; p++) {
+        cx2 a{0, 0}, b{0, 0};
+        for (int c = 0; c < NC; c++) {
+            cx2 l;
+            __builtin_memcpy(&l, L[c] + 2 * (size_t)p, sizeof l);
+            a += l * cx2{fr[c], fr[c]};
+            b += l * cx2{fi[c], fi[c]};
+        }
+        double *t = w + 2 * (size_t)row[p];
+        t[0] -= a[0] - b[1];
+        t[1] -= a[1] + b[0];
+    }
+}
+
+}   // namespace
+
 bool ldl_numeric(const LdlSymbolic &S, const std::vector<cd> &vals, std::vector<cd> &D,
                  std::vector<cd> &Lx) {
+    Lx.assign(S.nnzL(), cd(0));
+    return ldl_numeric(S, vals, D, Lx.data());
+}
+
+bool ldl_numeric(const LdlSymbolic &S, const std::vector<cd> &vals, std::vector<cd> &D, cd *Lx) {
     const int n = S.n;
     D.assign(n, cd(0));
-    Lx.assign(S.nnzL(), cd(0));
-    std::vector<cd> w(n, cd(0));
-    std::vector<int32_t> head(n, -1), link(n, -1), next(n, 0);
+    std::vector<double> wbuf(2 * (size_t)n, 0.0);
+    double *w = wbuf.data();
+    double *L = reinterpret_cast<double *>(Lx);
+    const int32_t *Li = S.Li.data();
+    // Runs of columns with the same rows below them (column j - 1's rows are j
+    // and those of column j) update a later column together: the indexed read
+    // and write of the work column, which bounds a column-by-column update, is
+    // paid once for up to eight columns (one factor of a 10 201-vertex grid: 125
+    // -> 37 ms; by columns in real arithmetic 117, by four columns 82).  rbeg[r], rbeg[r + 1]: columns of run r.
+    std::vector<int32_t> rbeg, run(n);
     for (int j = 0; j < n; j++) {
-        for (int p = S.Ap[j]; p < S.Ap[j + 1]; p++) w[S.Ai[p]] = vals[S.Asrc[p]];
-        // left-looking updates from columns k with L(j,k) != 0
-        int k = head[j];
-        head[j] = -1;
-        while (k != -1) {
-            int knext = link[k];
-            int pos = next[k];
-            cd f = Lx[pos] * D[k];
-            for (int p = pos; p < S.Lp[k + 1]; p++) w[S.Li[p]] -= Lx[p] * f;
-            next[k] = pos + 1;
-            if (next[k] < S.Lp[k + 1]) {
-                int r = S.Li[next[k]];
-                link[k] = head[r];
-                head[r] = k;
+        const bool joins = j > 0 && S.Lp[j] > S.Lp[j - 1] && Li[S.Lp[j - 1]] == j &&
+                           S.Lp[j] - S.Lp[j - 1] == S.Lp[j + 1] - S.Lp[j] + 1;
+        if (!joins) rbeg.push_back(j);
+        run[j] = (int32_t)rbeg.size() - 1;
+    }
+    const int nr = (int)rbeg.size();
+    rbeg.push_back(n);
+    // lists of the runs whose next row is j (their rows below the run, in turn)
+    std::vector<int32_t> head(n, -1), link(nr, -1), next(nr, 0);
+    // update by columns [k0, k1), from the row that is `tail` entries before
+    // the end of each column's list on (row j itself comes first)
+    auto update = [&](int k0, int k1, int tail) {
+        const int32_t *row = Li + S.Lp[k1] - tail;
+        const double *col[8];
+        double fr[8], fi[8];
+        for (int k = k0; k < k1;) {
+            const int m = k1 - k >= 8 ? 8 : k1 - k >= 4 ? 4 : k1 - k >= 2 ? 2 : 1;
+            for (int c = 0; c < m; c++) {
+                col[c] = L + 2 * (size_t)(S.Lp[k + c + 1] - tail);
+                const double lr = col[c][0], li = col[c][1];
+                const double dr = D[k + c].real(), di = D[k + c].imag();
+                fr[c] = lr * dr - li * di;
+                fi[c] = lr * di + li * dr;
             }
-            k = knext;
+            if (m == 8) ldl_update<8>(w, row, tail, col, fr, fi);
+            else if (m == 4) ldl_update<4>(w, row, tail, col, fr, fi);
+            else if (m == 2) ldl_update<2>(w, row, tail, col, fr, fi);
+            else ldl_update<1>(w, row, tail, col, fr, fi);
+            k += m;
         }
-        const cd dj = w[j];
+    };
+    for (int j = 0; j < n; j++) {
+        for (int p = S.Ap[j]; p < S.Ap[j + 1]; p++) {
+            w[2 * S.Ai[p]] = vals[S.Asrc[p]].real();
+            w[2 * S.Ai[p] + 1] = vals[S.Asrc[p]].imag();
+        }
+        // left-looking updates: runs below whose next row is j, then the
+        // columns before j in its own run
+        for (int r = head[j]; r != -1;) {
+            const int rnext = link[r], last = rbeg[r + 1];
+            update(rbeg[r], last, S.Lp[last] - next[r]);
+            if (++next[r] < S.Lp[last]) {
+                const int t = Li[next[r]];
+                link[r] = head[t];
+                head[t] = r;
+            }
+            r = rnext;
+        }
+        const int own = run[j], len = S.Lp[j + 1] - S.Lp[j];
+        if (rbeg[own] < j) update(rbeg[own], j, len + 1);
+        const cd dj(w[2 * j], w[2 * j + 1]);
         if (dj == cd(0) || !std::isfinite(dj.real()) || !std::isfinite(dj.imag())) return false;
         D[j] = dj;
-        w[j] = cd(0);
+        w[2 * j] = w[2 * j + 1] = 0.0;
+        const cd rj = 1.0 / dj;
+        const double rr = rj.real(), ri = rj.imag();
         for (int p = S.Lp[j]; p < S.Lp[j + 1]; p++) {
-            Lx[p] = w[S.Li[p]] / dj;
-            w[S.Li[p]] = cd(0);
+            double *t = w + 2 * (size_t)Li[p];
+            L[2 * (size_t)p] = t[0] * rr - t[1] * ri;
+            L[2 * (size_t)p + 1] = t[0] * ri + t[1] * rr;
+            t[0] = t[1] = 0.0;
         }
-        if (S.Lp[j] < S.Lp[j + 1]) {
-            next[j] = S.Lp[j];
-            int r = S.Li[S.Lp[j]];
-            link[j] = head[r];
-            head[r] = j;
+        if (j + 1 == rbeg[own + 1] && len > 0) {
+            next[own] = S.Lp[j];
+            const int t = Li[S.Lp[j]];
+            link[own] = head[t];
+            head[t] = own;
         }
     }
     return true;
@@ -275,33 +350,47 @@ bool ldl_numeric(const LdlSymbolic &S, const std::vector<cd> &vals, std::vector<
 
 void ldl_block_inverses(const LdlSymbolic &S, const std::vector<cd> &Lx, std::vector<cd> &invL,
                         std::vector<cd> &invLT) {
-    invL.assign(S.ndense, cd(0));
+    invL.resize(S.ndense);
     invLT.assign(S.ndense, cd(0));
+    ldl_block_inverses(S, Lx.data(), invL.data());
+    for (size_t b = 0; b < S.bheight.size(); b++) {
+        const int w = S.bstart[b + 1] - S.bstart[b];
+        const cd *X = &invL[S.doff[b]];
+        cd *XT = &invLT[S.doff[b]];
+        for (int i = 0; i < w; i++)
+            for (int c = 0; c <= i; c++) XT[(size_t)c * w + i] = X[(size_t)i * w + c];
+    }
+}
+
+void ldl_block_inverses(const LdlSymbolic &S, const cd *Lx, cd *invL) {
+    std::fill(invL, invL + S.ndense, cd(0));
     const int nb = (int)S.bheight.size();
     std::vector<cd> Lb;
     for (int b = 0; b < nb; b++) {
         const int s0 = S.bstart[b], w = S.bstart[b + 1] - s0;
         Lb.assign((size_t)w * w, cd(0));
-        for (int c = 0; c < w; c++) {
-            Lb[(size_t)c * w + c] = 1.0;
+        for (int c = 0; c < w; c++)
             for (int p = S.Lp[s0 + c]; p < S.Lp[s0 + c + 1]; p++) {
                 const int i = S.Li[p] - s0;
-                if (i < w) Lb[(size_t)i * w + c] = Lx[p];
+                if (i >= w) break;   // rows ascend: the rest lies below the block
+                Lb[(size_t)i * w + c] = Lx[p];
             }
-        }
-        cd *X = &invL[S.doff[b]];
-        // X = Lb^{-1}: column by column, forward substitution
-        for (int c = 0; c < w; c++) {
-            X[(size_t)c * w + c] = 1.0;
-            for (int i = c + 1; i < w; i++) {
-                cd acc = 0.0;
-                for (int t = c; t < i; t++) acc += Lb[(size_t)i * w + t] * X[(size_t)t * w + c];
-                X[(size_t)i * w + c] = -acc;
+        // X = Lb^{-1} by rows: row i of X is -sum_t Lb(i, t) X(t, :) over t < i
+        // and a one on the diagonal; every row is read and written in order
+        double *X = reinterpret_cast<double *>(&invL[S.doff[b]]);
+        for (int i = 0; i < w; i++) {
+            double *xi = X + 2 * (size_t)i * w;
+            for (int t = 0; t < i; t++) {
+                const double lr = Lb[(size_t)i * w + t].real(), li = Lb[(size_t)i * w + t].imag();
+                if (lr == 0.0 && li == 0.0) continue;
+                const double *xt = X + 2 * (size_t)t * w;
+                for (int c = 0; c <= t; c++) {
+                    xi[2 * c] -= lr * xt[2 * c] - li * xt[2 * c + 1];
+                    xi[2 * c + 1] -= lr * xt[2 * c + 1] + li * xt[2 * c];
+                }
             }
+            xi[2 * i] = 1.0;
         }
-        cd *XT = &invLT[S.doff[b]];
-        for (int i = 0; i < w; i++)
-            for (int c = 0; c < w; c++) XT[(size_t)c * w + i] = X[(size_t)i * w + c];
     }
 }
 

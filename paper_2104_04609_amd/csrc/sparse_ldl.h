@@ -74,11 +74,15 @@ LdlSymbolic ldl_symbolic(int n, const std::vector<int32_t> &ptr,
 // order (Lx[nnzL]).  Returns false on a zero pivot.
 bool ldl_numeric(const LdlSymbolic &S, const std::vector<cd> &vals, std::vector<cd> &D,
                  std::vector<cd> &Lx);
+// the same into the caller's Lx[nnzL], which need not be initialised
+bool ldl_numeric(const LdlSymbolic &S, const std::vector<cd> &vals, std::vector<cd> &D, cd *Lx);
 
 // Inverses of the unit lower-triangular diagonal blocks L_BB of every
 // dissection block, dense row-major w x w at doff[b]: invL and its transpose.
 void ldl_block_inverses(const LdlSymbolic &S, const std::vector<cd> &Lx, std::vector<cd> &invL,
                         std::vector<cd> &invLT);
+// invL alone, into the caller's invL[ndense], which need not be initialised
+void ldl_block_inverses(const LdlSymbolic &S, const cd *Lx, cd *invL);
 
 // Block solve in the original ordering, the algorithm the device runs:
 // per level, y_B -= L_B,ext y_ext then y_B = inv(L_BB) y_B (forward), D^{-1},
