@@ -511,28 +511,61 @@ struct LrBlock {
     int64_t uoff, voff, zoff;
 };
 
-__global__ __launch_bounds__(256) void hmat_z_kernel(const LrBlock *blocks, const float2 *V,
-                                                     const float2 *__restrict__ xt, int64_t N,
-                                                     double2 *z) {
-    const LrBlock B = blocks[blockIdx.x];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int n2 = 2 * B.n;
-    for (int l = wave; l < B.rank; l += 4) {
-        const float2 *v = V + B.voff + (int64_t)l * n2;
+// Bound by HBM (V, read once).  G lanes a rank index, two entries a load and four
+// loads in flight a lane.  A wavefront an index had two 8-byte loads a lane before
+// its sum over 64 lanes in the many small blocks; 16 lanes take 16 indices at once
+// (a product at 4 002 vertices 125 -> 115 us, at 10 242 401 -> 391 us).  Long rows
+// keep a wavefront: 1.87 ms at 40 962 vertices, 1.89 with 16 lanes everywhere,
+// 1.91 before.
+constexpr int Z_WIDE = 1024;   // entries of a row from which a wavefront takes it
+
+template <int G>
+__device__ __forceinline__ void z_block(const LrBlock &B, const float2 *__restrict__ V,
+                                        const float2 *__restrict__ xt, int64_t N,
+                                        double2 *__restrict__ z) {
+    const int lane = threadIdx.x % G, n2 = 2 * B.n;
+    const float2 *x = xt + B.c0;
+    const int64_t dphi = N - B.n;   // from the psi half's entries to the phi half's
+    for (int l = threadIdx.x / G; l < B.rank; l += 256 / G) {
+        // (rows have an even length and begin at even entries: 16-byte loads)
+        const float4 *v = reinterpret_cast<const float4 *>(V + B.voff + (int64_t)l * n2);
         double sr = 0, si = 0;
-#pragma unroll 4
-        for (int q = lane; q < n2; q += 64) {
-            const int d = q >= B.n ? 1 : 0;
-            const float2 a = v[q], b = xt[d * N + B.c0 + q - d * B.n];
-            sr += (double)a.x * b.x - (double)a.y * b.y;
-            si += (double)a.x * b.y + (double)a.y * b.x;
+        for (int q0 = lane; q0 < B.n; q0 += 4 * G) {
+            float4 a[4];
+            float2 x0[4], x1[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int q = q0 + u * G;
+                const bool in = q < B.n;
+                const int i = in ? 2 * q : 0;
+                a[u] = in ? v[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+                x0[u] = x[i + (i >= B.n ? dphi : 0)];
+                x1[u] = x[i + 1 + (i + 1 >= B.n ? dphi : 0)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (q0 + u * G >= B.n) break;
+                sr += (double)a[u].x * x0[u].x - (double)a[u].y * x0[u].y;
+                si += (double)a[u].x * x0[u].y + (double)a[u].y * x0[u].x;
+                sr += (double)a[u].z * x1[u].x - (double)a[u].w * x1[u].y;
+                si += (double)a[u].z * x1[u].y + (double)a[u].w * x1[u].x;
+            }
         }
-        for (int o = 32; o > 0; o >>= 1) {
-            sr += __shfl_xor(sr, o, 64);
-            si += __shfl_xor(si, o, 64);
+        for (int o = G / 2; o > 0; o >>= 1) {
+            sr += __shfl_xor(sr, o, G);
+            si += __shfl_xor(si, o, G);
         }
         if (lane == 0) z[B.zoff + l] = make_double2(sr, si);
     }
+}
+
+__global__ __launch_bounds__(256) void hmat_z_kernel(const LrBlock *__restrict__ blocks,
+                                                     const float2 *__restrict__ V,
+                                                     const float2 *__restrict__ xt, int64_t N,
+                                                     double2 *__restrict__ z) {
+    const LrBlock B = blocks[blockIdx.x];
+    if (2 * B.n < Z_WIDE) z_block<16>(B, V, xt, N, z);
+    else z_block<64>(B, V, xt, N, z);
 }
 
 // Rows of one test leaf: sum over the admissible blocks of its ancestors (root
@@ -547,7 +580,7 @@ __global__ __launch_bounds__(256) void hmat_z_kernel(const LrBlock *blocks, cons
 // serial loop per leaf, a workgroup of 128 threads each: 256 workgroups on the
 // 10 242-vertex sphere, 2.51 ms a launch, 2.69 ms a product.  Cut into ranges,
 // with a column per group of 2m threads and eight loads in flight, the chip is
-// full: 0.41 ms a product (1.2 GB, 3.0 TB/s).
+// full: 0.39 ms a product (1.2 GB, 3.1 TB/s).
 struct RowSeg {
     int64_t off, src;
     int stride, half, cnt, kind;

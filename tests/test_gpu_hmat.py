@@ -168,3 +168,24 @@ def test_hmat_leaf_sizes(P, leaf, n):
     ref = P.pmchwt_matvec(M, 2.0, 3.0, 1.5, x, precision="fp64").cpu().numpy()
     for sl in (slice(0, N), slice(N, 2 * N)):
         assert _rel(y[sl], ref[sl]) <= TOL
+
+
+@pytest.mark.parametrize("n", [13, 20, 32])
+def test_hmat_block_products(P, n):
+    """Block products z: row lengths below and above the length that a wavefront
+    takes (clusters of odd sizes up to 1 281 vertices), ranks that are no
+    multiple of the indices at once; repeated products are bitwise equal; against
+    the FP64 product at the compression's tolerance."""
+    import torch
+    from bem_inputs import geodesic_sphere
+    mesh = geodesic_sphere(n)
+    N = mesh.n_vertices
+    M = P.Mesh.from_inputs(mesh)
+    x = _dev(complex_normal(2 * N, seed=n))
+    print("hmat block products", N, flush=True)
+    y = P.pmchwt_matvec(M, 3.0, 4.0, 1.5, x, precision="fp32_hmat")
+    assert torch.equal(y, P.pmchwt_matvec(M, 3.0, 4.0, 1.5, x, precision="fp32_hmat"))
+    y = y.cpu().numpy()
+    ref = P.pmchwt_matvec(M, 3.0, 4.0, 1.5, x, precision="fp64").cpu().numpy()
+    for sl in (slice(0, N), slice(N, 2 * N)):
+        assert _rel(y[sl], ref[sl]) <= TOL
