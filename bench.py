@@ -86,8 +86,7 @@ def batch_measure(P, M, mesh, mf_step_s):
     """64 plane-wave right-hand sides (normalised Gaussian directions, seed
     2104) at 4 wavenumber pairs k_ext in {4, 8, 12, 16}, k_int = 1.5 k_ext,
     rho = 1.5: assembled complex64 operator x 64-column block on MFMA,
-    against the matrix-free FP32 operator on the same block (4 right-hand
-    sides per pair-kernel launch).  Then 8 plane waves solved in one lockstep
+    against the matrix-free FP32 operator on the same block.  Then 8 plane waves solved in one lockstep
     group against 8 single-wave solves (FP32 + refinement, assembled path)."""
     import torch
     from bem_inputs import wave_directions
@@ -376,7 +375,7 @@ def c3_leg(P, RL, rates, steps: int) -> dict:
         kern = kms / max(kn, 1)
         roof = (RL.pair_kernel_roofline(pairs, kern * 1e-3, "fp32", rates, symmetric=symmetric,
                                         lossy=True) if prec == "fp32"
-                else RL.pair_kernel_roofline(pairs, kern * 1e-3, "fp64"))
+                else RL.pair_kernel_roofline(pairs, kern * 1e-3, "fp64", symmetric=symmetric))
         out[f"{prec}_matvec"] = {"ms_per_step": step * 1e3, "kernel_ms": kern,
                                  "tri_pair_evals_per_s": T * (T - 1) / step, "roofline": roof}
     y64 = P.pmchwt_matvec(M, k0, k1, rho, x, precision="fp64")
@@ -632,7 +631,7 @@ def main():
     traffic = pmc_traffic()
     roof["traffic"] = traffic["bytes"] if traffic else None
     roof["traffic_detail"] = traffic
-    roof64 = RL.pair_kernel_roofline(pairs, kern64_ms * 1e-3, "fp64")
+    roof64 = RL.pair_kernel_roofline(pairs, kern64_ms * 1e-3, "fp64", symmetric=symmetric)
     value = T * (T - 1) / step_s
 
     solve = None

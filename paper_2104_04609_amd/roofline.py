@@ -15,10 +15,10 @@ rate of each transcendental instruction, measured on the device by
 ``bem_valu_rates``.  The roofline object reports achieved and peak in
 flop-equivalents at the P32 rate, so frac = achieved pairs/s / model pairs/s.
 FP64: table-based sin/cos and a refined 1/sqrt counted in flops (55 per
-pair), against the 78.6 TFLOP/s FP64 vector peak.  The symmetric FP32
-kernel (each separated triangle pair once) uses the unordered point pair
-as its unit: 164 flops (the accumulations twice) and the same 5
-transcendentals.
+pair), against the 78.6 TFLOP/s FP64 vector peak.  The symmetric kernels
+(each separated triangle pair once) use the unordered point pair as their
+unit: 164 flops (the accumulations twice) and the same 5 transcendentals
+(FP64: the same 55 flops).
 """
 from __future__ import annotations
 
@@ -112,7 +112,7 @@ def pair_kernel_roofline(point_pairs: int, seconds_per_launch: float,
                          precision: str = "fp32", rates: dict | None = None,
                          symmetric: bool = False, lossy: bool = False) -> dict:
     """point_pairs: ordered separated point pairs per matvec.  symmetric: the
-    FP32 kernel evaluates each unordered pair once (unit = unordered pair).
+    kernel evaluates each unordered pair once (unit = unordered pair).
     lossy: complex interior wavenumber, one more transcendental per pair (the
     decay e^{-Im(k) r} as exp2, priced at the 1/sqrt issue rate: both are
     quarter-rate transcendental instructions) and its multiply (2 flops)."""
@@ -156,6 +156,13 @@ def pair_kernel_roofline(point_pairs: int, seconds_per_launch: float,
         out["issue_frac"] = pairs_s * t_issue
         out["rates_measured"] = rates is not None
         return out
+    if symmetric:
+        fe = FLOPS_PER_UPAIR + FP64_TRANS_FLOPS_PER_PAIR
+        achieved = pairs_s / 2 * fe / 1e12
+        return {"bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
+                "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS, "traffic": None,
+                "work_unit": "unordered point pair", "flop_eq_per_unit": fe,
+                "units_per_s": pairs_s / 2, "point_pairs_per_s": pairs_s}
     fe = FLOPS_PER_PAIR + FP64_TRANS_FLOPS_PER_PAIR
     achieved = pairs_s * fe / 1e12
     return {"bound": "alu", "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
