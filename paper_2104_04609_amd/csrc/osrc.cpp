@@ -260,9 +260,8 @@ OsrcSymbolicState &symbolic(bem_mesh *m) {
     };
     // 1 (automatic; measured on the 10 242- and 40 962-vertex meshes): the
     // bottom-subtree schedule with the top levels one launch per level; plans
-    // with subtrees of up to 512 .. 4096 rows, each batch taking the one of
-    // up to OSRC_SUB_ROWS rows, or a larger one when that still gives
-    // OSRC_SUB_MIN_GROUPS workgroups.
+    // with subtrees of up to 512 .. 4096 rows, each batch taking one by its
+    // number of workgroups (split_view).
     // 2: the two-part solve with partial sums; 3: one bottom-subtree plan of
     // up to osrc.bottom_rows rows
     const int split_mode = tn.osrc_split.load();
@@ -320,16 +319,23 @@ LdlSplitDev split_view(const OsrcSymbolicState &sy, int ntasks, int nrhs) {
     if (sy.split_mode == 2 && sy.split.plan.ok) {
         sc = &sy.split;
     } else if (sy.nbottom > 0) {
-        // subtrees of up to OSRC_SUB_ROWS rows, larger ones while they still
-        // give OSRC_SUB_MIN_GROUPS workgroups
-        sc = &sy.bottom[0];
-        for (int i = 0; i < sy.nbottom; i++)
-            if (sy.bottom[i].rows <= OSRC_SUB_ROWS) sc = &sy.bottom[i];
-        for (int i = sy.nbottom - 1; i >= 0 && sy.bottom[i].rows > sc->rows; i--)
-            if ((int64_t)sy.bottom[i].plan.nsub * ntasks * nrhs >= OSRC_SUB_MIN_GROUPS) {
-                sc = &sy.bottom[i];
-                break;
-            }
+        // the smallest subtrees of at most OSRC_SUB_GROUPS workgroups; else those
+        // of up to OSRC_SUB_ROWS rows, larger ones while they still give
+        // OSRC_SUB_MIN_GROUPS workgroups
+        auto groups = [&](int i) { return (int64_t)sy.bottom[i].plan.nsub * ntasks * nrhs; };
+        int pick = 0;
+        while (pick < sy.nbottom && groups(pick) > OSRC_SUB_GROUPS) pick++;
+        if (pick == sy.nbottom) {
+            pick = 0;
+            for (int i = 0; i < sy.nbottom; i++)
+                if (sy.bottom[i].rows <= OSRC_SUB_ROWS) pick = i;
+            for (int i = sy.nbottom - 1; i > pick; i--)
+                if (groups(i) >= OSRC_SUB_MIN_GROUPS) {
+                    pick = i;
+                    break;
+                }
+        }
+        sc = &sy.bottom[pick];
     }
     if (!sc) return P;
     const LdlSplit &q = sc->plan;

@@ -14,11 +14,19 @@ struct PadeCoef {
     double2 A[PADE_MAX];
 };
 
-// Bottom-subtree plan of a batch: subtrees of up to OSRC_SUB_ROWS rows, or
-// larger ones when they still give OSRC_SUB_MIN_GROUPS workgroups (subtrees
-// x systems x vectors).
+// Bottom-subtree plan of a batch, by its workgroups (subtrees x systems x
+// vectors).  A workgroup fills a compute unit and its time goes with its rows, so
+// the best plan has the most workgroups that run at once, up to OSRC_SUB_GROUPS:
+// smaller subtrees leave more top levels (four launches each) and run in a second
+// round, larger ones leave compute units idle.  One apply, us, workgroups in
+// brackets: 2 562 vertices, 1 vector 93 (80) against 119 (20); 4 vectors 112 (160),
+// 124 (80), 137 (320); 10 242 vertices, 1 vector 153 (160), 164 (80), 176 (320);
+// 4 vectors 255 (160), 303 (320).  Where every plan has more, subtrees of up to
+// OSRC_SUB_ROWS rows, or larger ones that still give OSRC_SUB_MIN_GROUPS (10 242
+// vertices, 16 vectors 730 (640) against 775; 8 vectors 457 against 474 (320)).
+constexpr int OSRC_SUB_GROUPS = 256;
 constexpr int OSRC_SUB_ROWS = 2048;
-constexpr int OSRC_SUB_MIN_GROUPS = 1024;
+constexpr int OSRC_SUB_MIN_GROUPS = 512;
 
 // Largest dissection block (rows) a level workgroup can hold in LDS.
 constexpr int LDL_MAX_BLOCK = 4096;
