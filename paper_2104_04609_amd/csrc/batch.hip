@@ -114,14 +114,16 @@ template <> struct Mx<double> {
 __device__ __forceinline__ float fmaC(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmaC(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// sin and cos of the phase t (phase units): FP32 phases stay below 256
-// revolutions here, inside which the hardware functions reduce exactly
+// sin and cos of the phase t (phase units).  FP32 phases stay below 256
+// revolutions here, inside which the hardware functions reduce exactly; FP64 ones
+// below PHASE64_NARROW (the lossy variants are 5 % slower with the wide form,
+// which spills six more registers)
 __device__ __forceinline__ void sc_rev(float t, float &s, float &c, const double2 *) {
     s = __builtin_amdgcn_sinf(t);
     c = __builtin_amdgcn_cosf(t);
 }
 __device__ __forceinline__ void sc_rev(double t, double &s, double &c, const double2 *tab) {
-    DM<double>::sincos(t, s, c, tab);
+    sincos_256<false>(t, s, c, tab);
 }
 
 // w_j phi_b(y_j), read with a point index that is uniform over the wavefront

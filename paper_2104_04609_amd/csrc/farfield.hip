@@ -1405,7 +1405,7 @@ namespace {
 // Launch plan of the pair kernel for one precision and wavenumber pair.
 struct FarPlan {
     int code;      // 4 ck0 + 2 ck1 + multi
-    bool fr;       // phase reduction before v_sin/v_cos (FP32)
+    bool fr;       // phases beyond the batch kernel's; FP32: reduced before v_sin/v_cos
     int blk;       // test triangles per workgroup
     int nsplit;    // trial-triangle splits (grid.y)
 };
@@ -1417,7 +1417,7 @@ FarPlan far_plan(const bem_mesh *m, int precision, double2 k0, double2 k1, int b
     // largest phase in revolutions: max Re k * diameter / (2 pi)
     const double tmax = std::max(std::fabs(k0.x), std::fabs(k1.x)) * m->diameter *
                         0.15915494309189533576888376337251;
-    p.fr = precision != BEM_FP32 || tmax >= 256.0;
+    p.fr = tmax >= (precision == BEM_FP32 ? 256.0 : PHASE64_NARROW / PHASE64);
     p.blk = blk;
     const void *kern = precision == BEM_FP32
                            ? (p.fr ? far_kernel<float, true>(p.code)
@@ -1678,10 +1678,11 @@ void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, doubl
     const TuneEntry te = forced ? *forced : tune_lookup(m->T, R);
     const int blk = valid_block(te.block);
     const FarPlan plan = far_plan(m, precision, k0, nf.k1_plan, blk);
-    // vectors sharing every kernel evaluation (FP32 phases are not reduced there,
-    // so they stay below 256 revolutions)
+    // vectors sharing every kernel evaluation (phases stay below 256 revolutions
+    // there in FP32, where they are not reduced, and below 2^23 in FP64, whose table
+    // index has 32 bits)
     int r0 = 0;
-    if (te.multi >= 2 && !(precision == BEM_FP32 && plan.fr)) {
+    if (te.multi >= 2 && !plan.fr) {
         const int most = farfield_mx_max(precision);
         while (R - r0 >= FF_BATCH_MIN) {
             const int nr = std::min(most, R - r0);

@@ -255,6 +255,11 @@ __global__ __launch_bounds__(256) void field_kernel(
     // interior material of the enclosing object: omat[object] = (Re k, Im k, rho)
     const double2 k = ext ? k0 : make_double2(omat[3 * (reg - 1)], omat[3 * (reg - 1) + 1]);
     const double krev = k.x * (INV2PI * PHASE64);
+    // whole revolutions to the first trial point, taken off every phase: what is
+    // left does not grow with the point's distance
+    const double x0 = src[0] - px, y0 = src[1] - py, z0 = src[2] - pz;
+    const double turns =
+        PHASE64 * __builtin_rint(krev * sqrt(x0 * x0 + y0 * y0 + z0 * z0) * (1.0 / PHASE64));
     const double kdec = -k.y * 1.4426950408889634073599246810019;   // log2 of the decay
     const int t0 = blockIdx.y * split_len, t1 = min(T, t0 + split_len);
     double sr = 0, si = 0, dr = 0, di = 0;
@@ -286,7 +291,7 @@ __global__ __launch_bounds__(256) void field_kernel(
                 const double ri = rsqrt64(r2);
                 const double r = r2 * ri;
                 double Er, Ei;
-                sincos_256(krev * r, Ei, Er, etab);
+                sincos_256(__builtin_fma(krev, r, -turns), Ei, Er, etab);
                 if (LOSSY) {
                     const double d = decay64(kdec * r, xtab);
                     Er *= d;

@@ -7,6 +7,7 @@ namespace bem {
 
 // Phases of the FP64 kernels are counted in 256ths of a revolution.
 constexpr double PHASE64 = 256.0;
+constexpr double PHASE64_NARROW = 2147483648.0;   // sincos_256<false>: below it
 template <class R> constexpr double phase_unit() { return 1.0; }
 template <> constexpr double phase_unit<double>() { return PHASE64; }
 
@@ -21,7 +22,11 @@ __device__ __forceinline__ void phase_table(double2 *tab) {
 
 // sin and cos of 2 pi u / 256: u = n + f, |f| <= 1/2, the table entry n times
 // the series of the remainder c f, c = 2 pi / 256 (|c f| <= 0.0123: terms beyond
-// (c f)^6 are below 4e-18), cos - 1 and sin added to the entry last.
+// (c f)^6 are below 4e-18), cos - 1 and sin added to the entry last.  The entry is
+// taken from the low bits of n + 1.5 2^52, right while |u| < 2^51 (k r of 5e13).
+// WIDE = false converts n to 32 bits, which saturates from |u| = 2^31 on (k r of
+// 5e7), and is for the one kernel that has no register left for the addition.
+template <bool WIDE = true>
 __device__ __forceinline__ void sincos_256(double u, double &s, double &c,
                                            const double2 *__restrict__ tab) {
     constexpr double k = 6.283185307179586476925286766559 / 256.0, k2 = k * k;
@@ -31,7 +36,8 @@ __device__ __forceinline__ void sincos_256(double u, double &s, double &c,
     const double f = u - n, f2 = f * f;
     const double sn = __builtin_fma(__builtin_fma(f2, s5, s3), f2, s1) * f;
     const double cm = __builtin_fma(__builtin_fma(f2, c6, c4), f2, c2) * f2;   // cos - 1
-    const double2 e = tab[((int)n) & 255];
+    const int i = WIDE ? (int)__builtin_bit_cast(long long, n + 6755399441055744.0) : (int)n;
+    const double2 e = tab[i & 255];
     c = __builtin_fma(e.x, cm, __builtin_fma(-e.y, sn, e.x));
     s = __builtin_fma(e.y, cm, __builtin_fma(e.x, sn, e.y));
 }
