@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void winding_kernel(
                 const double c0 = v[6] - px, c1 = v[7] - py, c2 = v[8] - pz;
                 const double aa = a0 * a0 + a1 * a1 + a2 * a2, bb = b0 * b0 + b1 * b1 + b2 * b2,
                              cc = c0 * c0 + c1 * c1 + c2 * c2;
-                // (a point at a vertex: the norm is 0, as is its product)
+                // (a point at a vertex: the norm is 0, as are num and den)
                 const double ra = aa > 0 ? rsqrt64(aa) : 0.0, rb = bb > 0 ? rsqrt64(bb) : 0.0,
                              rc = cc > 0 ? rsqrt64(cc) : 0.0;
                 const double la = aa * ra, lb = bb * rb, lc = cc * rc;
@@ -186,6 +186,8 @@ __global__ __launch_bounds__(256) void winding_kernel(
                 // over 4 |a||b||c|: the modulus is at most 1, near 1 for small triangles
                 const double sc = 0.25 * ra * rb * rc;
                 const double nr = den * sc, ni = num * sc;
+                // a point at a vertex or on an edge of the triangle: no angle of its own
+                if (nr == 0 && ni == 0) continue;
                 const double wr = zr * nr - zi * ni, wi = zr * ni + zi * nr;
                 // arguments lie in (-pi, pi]: past pi, or past -pi
                 if (zi >= 0 && ni > 0 && wi < 0) turns++;
