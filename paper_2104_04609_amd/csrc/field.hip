@@ -189,9 +189,11 @@ __global__ __launch_bounds__(256) void winding_kernel(
                 // a point at a vertex or on an edge of the triangle: no angle of its own
                 if (nr == 0 && ni == 0) continue;
                 const double wr = zr * nr - zi * ni, wi = zr * ni + zi * nr;
-                // arguments lie in (-pi, pi]: past pi, or past -pi
-                if (zi >= 0 && ni > 0 && wi < 0) turns++;
-                if (zi < 0 && ni < 0 && wi >= 0) turns--;
+                // past pi, or past -pi.  The sign bit is the side that atan2 takes an
+                // argument of a zero imaginary part on (pi or -pi, 0 or -0)
+                const bool sz = __builtin_signbit(zi), sn = __builtin_signbit(ni),
+                           sw = __builtin_signbit(wi);
+                if (sz == sn && sn != sw) turns += sw ? 1 : -1;
                 zr = wr;
                 zi = wi;
             }
