@@ -40,6 +40,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "batch_split.h"
 #include "bem_internal.h"
 #include "entries.h"
 
@@ -59,7 +60,6 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr double INV4PI = 0.079577471545947667884441881686257;
 constexpr int BT_THREADS = 256;   // four wavefronts
 constexpr int BT_TAU = 16;        // test triangles per wavefront tile
-constexpr int BT_TILE = 32;       // trial triangles staged in LDS
 constexpr int BT_COLS = 16;       // real columns per matrix tile: 8 vectors
 constexpr int BT_BLK = 72;        // 4 complex 3 x 3 blocks
 // Weights of the sums over the test points.  w phi_a is o at the two other points
@@ -708,28 +708,11 @@ int batch_slots(const void *kern) {
     return cache[{dev, kern}] = std::max(1, cus * per);
 }
 
-// Trial-triangle ranges of a launch: whole staged tiles, the count that
-// minimises rounds of resident workgroups times the range's length.
-void batch_split(int T, int tiles, int slots, int *nsplit, int *len) {
-    const int nt = (T + BT_TILE - 1) / BT_TILE;
-    double best = 1e300;
-    for (int q = 1; q <= nt; q++) {   // q tiles per range
-        const int sp = (nt + q - 1) / q;
-        const double rounds = std::ceil((double)tiles * sp / slots);
-        const double cost = rounds * (q * BT_TILE + 4.0);   // + prologue and output
-        if (cost < best * (1 - 1e-12) || (cost <= best && sp < *nsplit)) {
-            best = cost;
-            *nsplit = sp;
-            *len = q * BT_TILE;
-        }
-    }
-}
-
 template <class R, int C>
 void batch_plan(const bem_mesh *m, int code, int *nsplit, int *len) {
     const int W = BT_THREADS / 64 / C, T = (int)m->T;
     batch_split(T, (T + W * BT_TAU - 1) / (W * BT_TAU), batch_slots((const void *)batch_fn<R, C>(code)),
-                nsplit, len);
+                (int64_t)T * 6 * BT_COLS * C * (int64_t)sizeof(double), nsplit, len);
 }
 
 template <class R, int C>
