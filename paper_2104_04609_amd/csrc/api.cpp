@@ -108,8 +108,8 @@ void mesh_trim(bem_mesh *m) {
     m->dyn32.release();
     m->partial.release();
     m->trirows.release();
-    m->sym_items.release();
-    m->sym_plan_id = nullptr;
+    m->sym32.release();
+    m->sym64.release();
     m->field_work->release();
     m->parts.clear();
     m->part_vidx.clear();
@@ -121,7 +121,7 @@ int64_t bem_mesh::device_bytes() const {
                 star_ptr.bytes() + star_idx.bytes() + near_pairs.bytes() + nf_rowptr.bytes() +
                 nf_col.bytes() + nf_cptr.bytes() + nf_contrib.bytes() + ss_tab.bytes() +
                 dyn64.bytes() + dyn32.bytes() + partial.bytes() + trirows.bytes() +
-                sym_items.bytes() + field_work->bytes();
+                sym32.items.bytes() + sym64.items.bytes() + field_work->bytes();
     for (const auto &kv : near_cache) b += kv.second->vals.bytes();
     for (const auto &kv : dense_cache) b += kv.second->bytes();
     for (const auto &kv : dense64_cache) b += kv.second->bytes();

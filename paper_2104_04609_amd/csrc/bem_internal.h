@@ -306,8 +306,17 @@ struct bem_mesh {
     bem::DevBuf<float> dyn32;
     bem::DevBuf<double> partial;
     bem::DevBuf<double> trirows;
-    bem::DevBuf<int32_t> sym_items;      // work items of the symmetric pair kernel
-    const void *sym_plan_id = nullptr;   // plan whose items sym_items holds
+    // work items of the symmetric pair kernel, and the plan that they are of: one set
+    // per precision, so that products of the two in turn leave each other's in place
+    struct SymItems {
+        bem::DevBuf<int32_t> items;
+        const void *plan = nullptr;
+        void release() {
+            items.release();
+            plan = nullptr;
+        }
+    };
+    SymItems sym32, sym64;
 
     // each object as a mesh of its own (block-diagonal Calderon
     // preconditioner; built on first use): part o holds object o's vertices

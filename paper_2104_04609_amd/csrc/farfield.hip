@@ -1609,11 +1609,12 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
         const SymPlan &sp = sym_plan_for<R>(m, plan);
         const size_t sneed = (size_t)(sp.tau_doubles + sp.sig_doubles + sp.acc_doubles);
         if (m->partial.n < sneed) m->partial.alloc(sneed);
-        if (m->sym_items.n < sp.items.size() || m->sym_plan_id != &sp) {
-            if (m->sym_items.n < sp.items.size()) m->sym_items.alloc(sp.items.size());
-            BEM_HIP(hipMemcpyAsync(m->sym_items.p, sp.items.data(), sp.items.size() * sizeof(int32_t),
+        bem_mesh::SymItems &si = F32 ? m->sym32 : m->sym64;
+        if (si.items.n < sp.items.size() || si.plan != &sp) {
+            if (si.items.n < sp.items.size()) si.items.alloc(sp.items.size());
+            BEM_HIP(hipMemcpyAsync(si.items.p, sp.items.data(), sp.items.size() * sizeof(int32_t),
                                    hipMemcpyHostToDevice, s));
-            m->sym_plan_id = &sp;
+            si.plan = &sp;
         }
         double *ptau = m->partial.p, *psig = ptau + sp.tau_doubles, *sigacc = psig + sp.sig_doubles;
         const dim3 gr((T + RED_TRI - 1) / RED_TRI);
@@ -1628,7 +1629,7 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
             for (size_t r = 0; r < nr; r++) {
                 const SymRound &rd = sp.rounds[r];
                 hipLaunchKernelGGL(fn, dim3(rd.nitems), dim3(blk), sym_smem<R>(blk), s, geo, dyn,
-                                   m->tobj_d.p, m->tri_d.p, T, m->sym_items.p + 3 * (int64_t)rd.item0,
+                                   m->tobj_d.p, m->tri_d.p, T, si.items.p + 3 * (int64_t)rd.item0,
                                    sp.chunk, cf, it, ptau, psig, rd.sig_base);
                 if (r + 1 < nr) accum(rd);   // the slots are reused by the next round
             }
