@@ -1601,6 +1601,7 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
     const dim3 gg((T + 255) / 256);
     hipLaunchKernelGGL(source_gather_kernel<R>, gg, dim3(256), 0, s, m->tri_d.p, m->tst.p, x, m->N, T,
                        dynb.p);
+    BEM_LAUNCH_CHECK();
     const Coef<R> cf = make_coef<R>(k0, nf);
     const Int<R> *it = interior_table<R>(m, nf, k0);
     const char *name = F32 ? "farfield_fp32" : "farfield_fp64";
@@ -1621,6 +1622,7 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
         auto accum = [&](const SymRound &rd) {
             hipLaunchKernelGGL(sym_sig_accum_kernel, gr, dim3(256), 0, s, psig, rd.sig_base, rd.b0,
                                rd.b1, T, blk, sigacc);
+            BEM_LAUNCH_CHECK();
         };
         {
             Timer tm(name, s);
@@ -1631,12 +1633,14 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
                 hipLaunchKernelGGL(fn, dim3(rd.nitems), dim3(blk), sym_smem<R>(blk), s, geo, dyn,
                                    m->tobj_d.p, m->tri_d.p, T, si.items.p + 3 * (int64_t)rd.item0,
                                    sp.chunk, cf, it, ptau, psig, rd.sig_base);
+                BEM_LAUNCH_CHECK();
                 if (r + 1 < nr) accum(rd);   // the slots are reused by the next round
             }
         }
         const SymRound &last = sp.rounds.back();
         hipLaunchKernelGGL(reduce_sym_kernel, gr, dim3(256), 0, s, ptau, psig, last.sig_base, last.b0,
                            last.b1, sigacc, m->tst.p, T, blk, sp.chunk, m->trirows.p);
+        BEM_LAUNCH_CHECK();
     } else {
         const int nsplit = plan.nsplit, split_len = (T + nsplit - 1) / nsplit;
         const size_t need = (size_t)nsplit * T * (ROW_STRIDE + 6);
@@ -1651,14 +1655,17 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
             else
                 dispatch_far<R, true>(grid, blk, s, geo, dyn, m->tobj_d.p, m->tri_d.p, T, split_len,
                                       cf, it, m->partial.p, ck0, ck1, multi);
+            BEM_LAUNCH_CHECK();
         }
         hipLaunchKernelGGL(reduce_splits_kernel, gg, dim3(256), 0, s, m->partial.p, m->tst.p, T, nsplit,
                            m->trirows.p);
+        BEM_LAUNCH_CHECK();
     }
     Timer tf("finalize", s);
     hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((m->N * NEAR_LANES + 255) / 256)), dim3(256), 0, s,
                        m->trirows.p, m->star_ptr.p, m->star_idx.p, m->nf_rowptr.p, m->nf_col.p,
                        (const double2 *)nf.vals.p, m->nf_nnz, x, m->N, y);
+    BEM_LAUNCH_CHECK();
 }
 
 }   // namespace
