@@ -558,8 +558,8 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float *__restric
                                                           int nchunks, int64_t M, int Np, int R,
                                                           double2 *__restrict__ y) {
     __shared__ double2 tile[32][33];
-    const int64_t m0 = (int64_t)blockIdx.x * 32;
-    const int r0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int64_t m0 = (int64_t)blockIdx.y * 32;
+    const int r0 = blockIdx.x * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     for (int q = ty; q < 32; q += 8) {
         const int64_t m = m0 + q;
         double2 v = make_double2(0.0, 0.0);
@@ -636,8 +636,9 @@ template <class R, int NT> constexpr int mx_step() { return MxOp<R>::VE * mx_lpr
 template <class R>
 __global__ __launch_bounds__(256) void mx_prep_kernel(const double2 *__restrict__ x, int nr,
                                                       int64_t K, R *__restrict__ XT) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int r = blockIdx.y;
+    // (vectors along x: their number is not bounded by a grid's y extent)
+    const int64_t k = (int64_t)blockIdx.y * 256 + threadIdx.x;
+    const int r = blockIdx.x;
     if (k >= K) return;
     const double2 v = r < nr ? x[(int64_t)r * K + k] : make_double2(0.0, 0.0);
     R *re = XT + (int64_t)(2 * r) * 2 * K, *im = re + 2 * K;
@@ -998,7 +999,7 @@ void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, cha
     const int nsplit = (int)((Kp + klen - 1) / klen);
     R *XT = (R *)scratch;
     double *part = (double *)(scratch + 16 * NT * Kp * (int64_t)sizeof(R));
-    hipLaunchKernelGGL(mx_prep_kernel<R>, dim3((unsigned)((n2 + 255) / 256), 8 * NT), dim3(256), 0, s, x,
+    hipLaunchKernelGGL(mx_prep_kernel<R>, dim3(8 * NT, (unsigned)((n2 + 255) / 256)), dim3(256), 0, s, x,
                        nr, n2, XT);
     BEM_LAUNCH_CHECK();
     {
@@ -1181,7 +1182,7 @@ void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hi
         Xp = own_x.p;
         Yp = own_y.p;
     }
-    hipLaunchKernelGGL(mx_prep_kernel<float>, dim3((unsigned)((K + 255) / 256), Rp), dim3(256), 0, s, x, R,
+    hipLaunchKernelGGL(mx_prep_kernel<float>, dim3(Rp, (unsigned)((K + 255) / 256)), dim3(256), 0, s, x, R,
                        K, Xp);
     BEM_LAUNCH_CHECK();
     {
@@ -1191,7 +1192,7 @@ void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hi
                            (const float *)op.B.p, Xp, Yp, M, Kp, Np, kchunk);
         BEM_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((M + 31) / 32), (R + 31) / 32), dim3(256), 0, s,
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3((R + 31) / 32, (unsigned)((M + 31) / 32)), dim3(256), 0, s,
                        Yp, nchunks, M, Np, R, y);
     BEM_LAUNCH_CHECK();
     BEM_HIP(hipStreamSynchronize(s));   // the workspace is free again, or released
