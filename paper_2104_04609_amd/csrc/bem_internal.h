@@ -373,8 +373,10 @@ bool tune_find(int64_t T, int R, TuneEntry *e);
 void farfield_apply(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
                     double rho, const double2 *x, double2 *y, int precision,
                     hipStream_t s, int block = 0);
-// y_r = B x_r for R right-hand sides ([R][2N]); two or more share each kernel
-// evaluation
+// y_r = B x_r for R right-hand sides ([R][2N]); farfield_batch_min or more share
+// each kernel evaluation (its time hardly depends on their number; 6 252 vertices,
+// ms for 2 to 8 vectors: FP32 12.5 against 5.4 a vector alone, FP64 25 against 10.9)
+constexpr int farfield_batch_min = 3;
 // Launch parameters: tune_lookup(T, R) unless `forced` is given.
 void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, double2 k1,
                           double rho, const double2 *x, double2 *y, int R, int precision,

@@ -1554,11 +1554,6 @@ template <class R> const SymPlan &sym_plan_for(const bem_mesh *m, const FarPlan 
 
 }   // namespace
 
-// Vectors from which the batch kernel is used: its time hardly depends on the
-// number of vectors.  6 252 vertices, ms for 2 to 8 vectors: FP32 12.5 against
-// 5.4 a vector alone, FP64 25 against 10.9.
-constexpr int FF_BATCH_MIN = 3;
-
 // Upper bound over every block size and the batch kernel's launches, so that
 // it holds whatever the tuning table says.
 int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, double2 k1, int R) {
@@ -1576,7 +1571,7 @@ int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, dou
                                       (int64_t)sp.items.size() * 4);
         }
     }
-    if (R >= FF_BATCH_MIN) part = std::max(part, farfield_mx_bytes(m, precision, k0, k1, R));
+    if (R >= farfield_batch_min) part = std::max(part, farfield_mx_bytes(m, precision, k0, k1, R));
     return dyn + part + T * ROW_STRIDE * 8;
 }
 
@@ -1692,7 +1687,7 @@ void farfield_apply_batch(bem_mesh *m, const NearOperator &nf, double2 k0, doubl
     int r0 = 0;
     if (te.multi >= 2 && !plan.fr) {
         const int most = farfield_mx_max(precision);
-        while (R - r0 >= FF_BATCH_MIN) {
+        while (R - r0 >= farfield_batch_min) {
             const int nr = std::min(most, R - r0);
             farfield_mx_apply(m, nf, k0, x + r0 * n2, y + r0 * n2, nr, precision, s);
             r0 += nr;

@@ -179,7 +179,9 @@ TuneEntry autotune(bem_mesh *m, double2 k0, double2 k1, double rho, int R, int e
     best.t_mf = 1e300;
     for (int blk : {64, 128, 256})
         for (int mm : {1, 2}) {   // one vector per launch, or shared launches
-            if (mm > 1 && mm > R) continue;
+            // shared from farfield_batch_min vectors on: for two the choice makes no
+            // difference, and their entry, which serves three as well, shares
+            if (mm == 1 ? R > 1 && R < farfield_batch_min : R == 1) continue;
             TuneEntry c = best;
             c.block = blk;
             c.multi = mm;
