@@ -508,9 +508,12 @@ int bem_profile_read(const char *kernel, double *total_ms, int64_t *launches);
  *                         MiB (1..65536, default 4096: one launch up to about
  *                         60 000 vertices); larger meshes run the test blocks
  *                         in several launches, results unchanged
- *   "dense.skinny_min_rhs" accepted and returned, without effect: products with
- *                         the assembled operator below gemm_min take the
- *                         vector or the matrix units by their count
+ *   "dense.skinny_min_rhs" right-hand-side count (>= 2) from which products
+ *                         with the assembled complex64 operator below gemm_min
+ *                         run on the matrix units; below it on the vector
+ *                         units, up to 8 vectors per pass.  24 (the default):
+ *                         the faster by count and size.  Holds for every shape,
+ *                         autotuned or not
  *   "dense.gemm_min_rhs"  right-hand-side count from which the assembled
  *                         operator is applied with the MFMA GEMM instead of
  *                         the products that read the operator once per 32
@@ -606,7 +609,7 @@ typedef struct {
     int block;               /* test triangles per pair-kernel workgroup */
     int multi;               /* right-hand sides per pair-kernel launch */
     int gemm_min;            /* assembled path: MFMA GEMM from this many vectors */
-    int skinny_min;          /* without effect */
+    int skinny_min;          /* kept for saved entries, without effect */
     int path;                /* -1 no preference, 0 matrix-free, 1 assembled */
     double t_matrix_free;    /* seconds per operator application to n_rhs vectors */
     double t_assembled;      /* same on the assembled operator (0 if not timed) */

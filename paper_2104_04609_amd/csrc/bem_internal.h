@@ -330,6 +330,9 @@ struct bem_mesh {
 
 namespace bem {
 
+// Value of "dense.skinny_min_rhs" that leaves the choice of units to the count.
+constexpr int DENSE_SKINNY_BY_COUNT = 24;
+
 // Process-wide default launch parameters (bem_tune_set / bem_tune_get).
 struct Tuning {
     std::atomic<int> farfield_multi_max{4};   // >= 2: pair-kernel launches shared by several vectors
@@ -337,7 +340,7 @@ struct Tuning {
     std::atomic<int> farfield_symmetric{1};   // single vector: each separated pair once
     std::atomic<int> farfield_sym_round_mib{4096};   // symmetric kernel: sigma partials per launch
     std::atomic<int> dense_gemm_min_rhs{33};  // MFMA GEMM from this many right-hand sides
-    std::atomic<int> dense_skinny_min_rhs{24}; // kept for callers that set it: the count decides
+    std::atomic<int> dense_skinny_min_rhs{DENSE_SKINNY_BY_COUNT};   // matrix units from this many
     std::atomic<int> solve_refine_update{1};  // FP32 refinement: later residuals updated in FP32
     std::atomic<int> solve_residual_dense_gib{32};   // complex128 operator for FP32-path residuals
     // compressed operator (read when one is built)
@@ -361,7 +364,7 @@ struct TuneEntry {
     int block = 256;           // test triangles per pair-kernel workgroup: 64, 128, 256
     int multi = 4;             // 1: one right-hand side per pair-kernel launch; 2, 4: shared
     int gemm_min = 33;         // MFMA GEMM from this many right-hand sides
-    int skinny_min = 24;       // without effect (kept in the saved lines)
+    int skinny_min = DENSE_SKINNY_BY_COUNT;   // kept in the saved lines, without effect
     int path = -1;             // FP32 solves: -1 no preference, 0 matrix-free, 1 assembled
     double t_mf = 0, t_dense = 0, t_asm = 0;   // seconds (R vectors; assembly)
 };

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void dense_gemv64_kernel(const double2 *__rest
         for (int q = 0; q < nrow; q++) y[row0 + q] = make_double2(sr[q], si[q]);
 }
 
-// y_r = B x_r for NR vectors (2..7); x: [NR][n2] complex64, y_r = y + r ystride.
+// y_r = B x_r for NR vectors (2..8); x: [NR][n2] complex64, y_r = y + r ystride.
 // Bound by HBM if the loads of B never wait.  Two rows per wavefront; each chunk of
 // the NR vectors is staged in LDS by the workgroup and read by all its rows (each
 // LDS value once per wavefront, for both of its rows).  Up to five vectors the next
@@ -1052,7 +1052,12 @@ void launch_gemv(const DenseOperator &op, const float2 *xs, double2 *y, hipStrea
 // vectors, vector and matrix units: 5 124 rows 50 54 72 78 and 62 for any number;
 // 10 584 rows 172 187 210 227 and 208; 20 484 rows 617 655 639 701 and 740.  At 8
 // the vector units need 1 104 us there.
-int gemv_max_rhs(int64_t n2) { return n2 >= 10000 ? 7 : 5; }
+int gemv_max_rhs(int64_t n2) {
+    const int line = tuning().dense_skinny_min_rhs;
+    if (line != DENSE_SKINNY_BY_COUNT) return line - 1;   // the caller's choice
+    return n2 >= 10000 ? 7 : 5;
+}
+constexpr int GEMV_RHS = 8;   // vectors of a launch on the vector units at most
 
 }   // namespace
 
@@ -1067,6 +1072,7 @@ void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, De
             nr = mx_group(nr);
             mx_apply((const float *)op.B.p, n2, xr, yr, nr, xs, s);
         } else {
+            nr = std::min(nr, GEMV_RHS);
             const int64_t cnt = nr * n2;
             if (xs.n < (size_t)cnt) xs.alloc((size_t)cnt);
             hipLaunchKernelGGL(to_c64_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, xr,
@@ -1084,7 +1090,8 @@ void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, De
             case 4: launch_gemv<4>(op, xs.p, yr, s); break;
             case 5: launch_gemv<5>(op, xs.p, yr, s); break;
             case 6: launch_gemv<6>(op, xs.p, yr, s); break;
-            default: launch_gemv<7>(op, xs.p, yr, s); break;
+            case 7: launch_gemv<7>(op, xs.p, yr, s); break;
+            default: launch_gemv<8>(op, xs.p, yr, s); break;
             }
             BEM_LAUNCH_CHECK();
         }
