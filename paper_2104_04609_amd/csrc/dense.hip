@@ -1047,15 +1047,24 @@ void launch_gemv(const DenseOperator &op, const float2 *xs, double2 *y, hipStrea
                        dim3(64 * gv_waves<NR>()), 0, s, op.B.p, op.n2, xs, y, op.n2);
 }
 
-// Vectors up to which the complex64 product runs on the vector units: five, or
-// seven on 10 000 rows and more, where they keep up with HBM.  us for 4, 5, 6, 7
+// Small operators are bound by their launches: the product on the vector units has
+// one less than that on the matrix units (two against three).  us for 6, 7 and 8
+// vectors, vector and matrix units: 324 rows 13.5 13.9 15.3 and 16.5; 504 rows 13.5
+// 14.1 15.6 and 16.5; 724 rows 15.4 16.9 18.8 and 16.4.  complex128, two vectors, two
+// single products against one on the matrix units: 324 rows 24.0 and 25.5, 504 rows
+// 28.8 and 25.4.
+constexpr int64_t GEMV_SMALL_ROWS = 600, GEMV64_SMALL_ROWS = 400;
+
+// Vectors up to which the complex64 product runs on the vector units: all eight of a
+// launch on small operators, else five, or seven on 10 000 rows and more, where they
+// keep up with HBM.  us for 4, 5, 6, 7
 // vectors, vector and matrix units: 5 124 rows 50 54 72 78 and 62 for any number;
 // 10 584 rows 172 187 210 227 and 208; 20 484 rows 617 655 639 701 and 740.  At 8
 // the vector units need 1 104 us there.
 int gemv_max_rhs(int64_t n2) {
     const int line = tuning().dense_skinny_min_rhs;
     if (line != DENSE_SKINNY_BY_COUNT) return line - 1;   // the caller's choice
-    return n2 >= 10000 ? 7 : 5;
+    return n2 <= GEMV_SMALL_ROWS ? 8 : n2 >= 10000 ? 7 : 5;
 }
 constexpr int GEMV_RHS = 8;   // vectors of a launch on the vector units at most
 
@@ -1145,10 +1154,11 @@ void dense_apply(const DenseOperator &op, const double2 *x, double2 *y, int R,
                  DevBuf<float2> &xs, hipStream_t s, const TuneEntry *forced) {
     if (op.fp64) {
         for (int r0 = 0; r0 < R;) {
-            const int nr = mx_group(R - r0);
+            int nr = mx_group(R - r0);
+            if (nr == 2 && op.n2 <= GEMV64_SMALL_ROWS) nr = 1;
             const double2 *xr = x + r0 * op.n2;
             double2 *yr = y + r0 * op.n2;
-            if (nr >= 2) {
+            if (nr > 1) {
                 mx_apply((const double *)op.B64.p, op.n2, xr, yr, nr, xs, s);
             } else {
                 Timer tm("dense_gemv_fp64", s);
