@@ -1056,15 +1056,18 @@ void launch_gemv(const DenseOperator &op, const float2 *xs, double2 *y, hipStrea
 constexpr int64_t GEMV_SMALL_ROWS = 600, GEMV64_SMALL_ROWS = 400;
 
 // Vectors up to which the complex64 product runs on the vector units: all eight of a
-// launch on small operators, else five, or seven on 10 000 rows and more, where they
-// keep up with HBM.  us for 4, 5, 6, 7
-// vectors, vector and matrix units: 5 124 rows 50 54 72 78 and 62 for any number;
-// 10 584 rows 172 187 210 227 and 208; 20 484 rows 617 655 639 701 and 740.  At 8
-// the vector units need 1 104 us there.
+// launch on small operators, else five, or seven on 11 000 rows and more.  The matrix
+// units take the same time for any number up to 8.  us, vector units for 5, 6, 7 and
+// 8 vectors, and matrix units: 5 124 rows 51 66 70 113 and 61; 8 824 rows 137 170 182
+// 255 and 147; 10 584 rows 179 202 215 298 and 204; 11 524 rows 212 225 239 329 and
+// 244; 12 504 rows 275 262 279 452 and 277; 16 824 rows 422 480 511 738 and 502; 20 484
+// rows 643 637 693 1 051 and 733.  (Six and seven run in rounds of 8 192 rows: on
+// 5 784 to 8 004 rows, just below a round, they are the faster form as well, 106 and
+// 111 against 128 us on 8 004.)
 int gemv_max_rhs(int64_t n2) {
     const int line = tuning().dense_skinny_min_rhs;
     if (line != DENSE_SKINNY_BY_COUNT) return line - 1;   // the caller's choice
-    return n2 <= GEMV_SMALL_ROWS ? 8 : n2 >= 10000 ? 7 : 5;
+    return n2 <= GEMV_SMALL_ROWS ? 8 : n2 >= 11000 ? 7 : 5;
 }
 constexpr int GEMV_RHS = 8;   // vectors of a launch on the vector units at most
 
