@@ -27,6 +27,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "bem_internal.h"
 #include "fp64_math.h"
@@ -144,30 +145,28 @@ __global__ __launch_bounds__(256) void winding_kernel(
         const int64_t pp = list[min(idx0, count - 1)];
         const double px = pts[3 * pp], py = pts[3 * pp + 1], pz = pts[3 * pp + 2];
         const int t0 = split * len, t1 = min(T, t0 + len);
-        double om = 0.0, ow = 0.0, zr = 1.0, zi = 0.0;
-        int turns = 0, obj = -1;
+        struct Sums {
+            double om = 0.0, ow = 0.0;     // closed sums
+            double zr = 1.0, zi = 0.0;     // running product
+            int turns = 0, obj = -1;
+            bool lost = false;             // a product that was closed was zero
+        } s;
         auto close = [&]() {   // the product's argument into the sums
-            const double o = 2.0 * (atan2(zi, zr) + TWO_PI * turns);
-            om += o;
-            ow += o * (obj + 1);
-            zr = 1.0;
-            zi = 0.0;
-            turns = 0;
+            const double o = 2.0 * (atan2(s.zi, s.zr) + TWO_PI * s.turns);
+            s.om += o;
+            s.ow += o * (s.obj + 1);
+            s.lost = s.lost || (s.zr == 0 && s.zi == 0);
+            s.zr = 1.0;
+            s.zi = 0.0;
+            s.turns = 0;
         };
-        for (int base = t0; base < t1; base += FT) {
-            const int cnt = min(FT, t1 - base);
-            __syncthreads();
-            for (int idx = threadIdx.x; idx < cnt * WS; idx += 256) {
-                const int sl = idx / WS, f = idx - sl * WS;
-                const int64_t t = base + sl;
-                tile[idx] = f < 9 ? P[3 * tri[3 * t + f / 3] + f % 3] : (double)tobj[t];
-            }
-            __syncthreads();
+        // the triangles of the staged tile; `skip`: leaves out factors that are zero
+        auto sweep = [&](int cnt, auto skip) {
             for (int sl = 0; sl < cnt; sl++) {
                 const double *v = tile + sl * WS;
-                if ((int)v[9] != obj) {   // uniform
-                    if (obj >= 0) close();
-                    obj = (int)v[9];
+                if ((int)v[9] != s.obj) {   // uniform
+                    if (s.obj >= 0) close();
+                    s.obj = (int)v[9];
                 }
                 const double a0 = v[0] - px, a1 = v[1] - py, a2 = v[2] - pz;
                 const double b0 = v[3] - px, b1 = v[4] - py, b2 = v[5] - pz;
@@ -186,27 +185,45 @@ __global__ __launch_bounds__(256) void winding_kernel(
                 // over 4 |a||b||c|: the modulus is at most 1, near 1 for small triangles
                 const double sc = 0.25 * ra * rb * rc;
                 const double nr = den * sc, ni = num * sc;
-                // a point at a vertex or on an edge of the triangle: no angle of its own
-                if (nr == 0 && ni == 0) continue;
-                const double wr = zr * nr - zi * ni, wi = zr * ni + zi * nr;
+                if (skip.value && nr == 0 && ni == 0) continue;
+                const double wr = s.zr * nr - s.zi * ni, wi = s.zr * ni + s.zi * nr;
                 // past pi, or past -pi.  The sign bit is the side that atan2 takes an
                 // argument of a zero imaginary part on (pi or -pi, 0 or -0)
-                const bool sz = __builtin_signbit(zi), sn = __builtin_signbit(ni),
+                const bool sz = __builtin_signbit(s.zi), sn = __builtin_signbit(ni),
                            sw = __builtin_signbit(wi);
-                if (sz == sn && sn != sw) turns += sw ? 1 : -1;
-                zr = wr;
-                zi = wi;
+                if (sz == sn && sn != sw) s.turns += sw ? 1 : -1;
+                s.zr = wr;
+                s.zi = wi;
+            }
+        };
+        for (int base = t0; base < t1; base += FT) {
+            const int cnt = min(FT, t1 - base);
+            __syncthreads();
+            for (int idx = threadIdx.x; idx < cnt * WS; idx += 256) {
+                const int sl = idx / WS, f = idx - sl * WS;
+                const int64_t t = base + sl;
+                tile[idx] = f < 9 ? P[3 * tri[3 * t + f / 3] + f % 3] : (double)tobj[t];
+            }
+            __syncthreads();
+            const Sums before = s;
+            sweep(cnt, std::false_type{});
+            // a product of zero: the point is at a vertex or on an edge of some triangle,
+            // which has no angle of its own; the tile again without such triangles
+            if (s.lost || (s.zr == 0 && s.zi == 0)) {
+                s = before;
+                sweep(cnt, std::true_type{});
+                s.lost = false;
             }
             // keep the product's size (its argument stays)
-            const double big = fmax(fabs(zr), fabs(zi));
+            const double big = fmax(fabs(s.zr), fabs(s.zi));
             const double inv = big > 0 ? 1.0 / big : 1.0;
-            zr *= inv;
-            zi *= inv;
+            s.zr *= inv;
+            s.zi *= inv;
         }
-        if (obj >= 0) close();
+        if (s.obj >= 0) close();
         if (idx0 < count) {
-            part[2 * ((int64_t)split * count + idx0)] = om;
-            part[2 * ((int64_t)split * count + idx0) + 1] = ow;
+            part[2 * ((int64_t)split * count + idx0)] = s.om;
+            part[2 * ((int64_t)split * count + idx0) + 1] = s.ow;
         }
     }
 }
