@@ -582,16 +582,18 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float *__restric
 // ----------------------------- up to 32 right-hand sides: skinny MFMA product
 // The same real product with 16 NT columns (8 NT complex right-hand sides) on
 // v_mfma_f32_16x16x4 / v_mfma_f64_16x16x4, for the complex64 and the complex128
-// operator.  Bound by HBM (every entry of B once per launch); the matrix cores
-// need 0.18 ms for 8 vectors at 10 242 vertices, B 0.52 ms at the rate of the
-// one-vector product.  A wavefront streams 16 RT rows over its range of K with
-// 16-byte loads of 256 or 512 contiguous bytes a row, the next step's loads in
-// flight, and turns them through LDS (loads in the operand's own order read 64
-// bytes a row, 20 % slower; 8 vectors on the vector units took 1.10 ms, complex128
-// one by one 8.3 ms, here 1.24);
-// the columns come from XT[16 NT][Kp] through the caches.  The 4 k-slots of a matrix instruction may hold any 4 values of k as
-// long as A and XT agree: lane (i, q) = (lane % 16, lane / 16) holds VE values of
-// row i from k = kb + VE (4 c + q) on, and instruction (c, e) takes the e-th.
+// operator.  Up to 8 vectors bound by HBM (every entry of B once per launch): at
+// 10 242 vertices the FP64 matrix cores need 0.37 ms for 8 vectors, at the 72 TFLOP/s
+// of a large product, and B 0.52 ms at the rate of the one-vector product; 9 to 16
+// vectors are bound by the matrix cores (0.75 ms, measured 1.00).  A wavefront
+// streams 16 RT rows over its range of K with 16-byte loads of 256 or 512 contiguous
+// bytes a row, the next step's loads in flight, and turns them through LDS (loads in
+// the operand's own order read 64 bytes a row, 20 % slower; 8 vectors on the vector
+// units took 1.10 ms, complex128 one by one 8.3 ms, here 0.74 and 1.24); the columns
+// come from XT[16 NT][Kp] through the caches.  The 4 k-slots of a matrix instruction
+// may hold any 4 values of k as long as A and XT agree: lane (i, q) = (lane % 16,
+// lane / 16) holds VE values of row i from k = kb + VE (4 c + q) on, and instruction
+// (c, e) takes the e-th.
 template <class R> struct MxOp;
 template <> struct MxOp<float> {
     typedef float Vec __attribute__((ext_vector_type(4)));
@@ -625,8 +627,8 @@ template <class R, int NT> constexpr int mx_waves() {
 // FP64 (exact products of FP32 values): FP32 matrix instructions add four products
 // into the sum each, and even sums of 8 products had an error above that of the
 // vector units (1.4e-7 against 1.3e-7, 1.9e-7 for sums of 64); FP64 gives
-// 1.2e-7, and B still costs more than the matrix cores (0.42 ms for 8 vectors).  Beyond, FP32 in
-// sums of 64 added in FP64, as against 8.6e-7 of the MFMA GEMM it took over from.
+// 1.2e-7, and for 8 vectors B still costs more than the matrix cores.  Beyond, FP32
+// in sums of 64 added in FP64, as against 8.6e-7 of the MFMA GEMM it took over from.
 template <class R, int NT>
 using MxWork = std::conditional_t<std::is_same<R, double>::value || NT <= 2, double, float>;
 template <class R, int NT> constexpr int mx_step() { return MxOp<R>::VE * mx_lpr<R, NT>(); }   // of K
@@ -1028,7 +1030,8 @@ void mx_apply(const T *B, int64_t n2, const double2 *x, double2 *y, int nr, DevB
 }
 
 // right-hand sides of the next launch when `left` remain: 24 to 32 share one (four
-// column tiles; below, 16 and the rest apart are no slower and keep short sums)
+// column tiles), below, 16 and the rest apart keep the FP64 sums (20 vectors at 10 242
+// vertices 1.67 ms, against 1.22 for 24 to 32 together)
 int mx_group(int left) { return left >= 24 ? std::min(left, MX_MAX_RHS) : std::min(left, 16); }
 
 }   // namespace

@@ -1463,12 +1463,16 @@ template <class R> SymFn<R> sym_kernel(int code, bool fr) {
 // Chunk length: an item costs about as much as four more trial triangles
 // (loading its test triangles, storing their rows), and the launch ends with
 // half a chunk of idle slots, so with w trial triangles of work per resident
-// workgroup the time is about w (1 + 4 / L) + L, least at L = 2 sqrt(w).
-// Measured optima (two workgroups a CU): 4 at 720 triangles, 8 at 1 280, 12 to
-// 24 at 2 880, 24 at 5 120 and 8 000, 64 at 12 500, 64 to 96 at 20 480, flat
-// from 64 to 300 at 40 500.  A list-schedule model, which took the slots as
-// independent, chose chunks two to eight times longer: 0.21 -> 0.09 ms at 1 280
-// triangles, 14.7 -> 14.1 at 20 480, 61.6 -> 54.6 at 40 500.
+// workgroup the time is about w (1 + 4 / L) + L, least at L = 2 sqrt(w).  The
+// formula knows no whole rounds of workgroups and is within 3 % of the measured
+// optimum (two workgroups a CU; chosen length and time against the best one, us,
+// FP32): 4 at 720 triangles 62.5, the best; 4 at 1 280 106 against 103 (8); 12 at
+// 2 880 358, the best; 20 at 5 120 1 013 against 998 (24); 32 at 8 000 2 290 against
+// 2 262 (24); 64 at 12 500 5 335, the best; 96 at 20 480 14 149, as 64; 192 at 40 500
+// 54 405, flat from 64 on; FP64 4 at 1 280 175 against 170 (8), 20 at 5 120 1 981
+// against 1 935 (24), 64 at 12 500 the best.  A list-schedule model, which took the
+// slots as independent, chose chunks two to eight times longer: 0.21 -> 0.11 ms at
+// 1 280 triangles, 14.7 -> 14.1 at 20 480, 61.6 -> 54.6 at 40 500.
 constexpr int SYM_CHUNK_MAX = 96;
 constexpr int64_t SYM_ITEMS_MAX = 16384;   // bounds the tau rows (0.6 GB at 256)
 struct SymRound {

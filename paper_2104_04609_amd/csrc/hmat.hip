@@ -580,7 +580,7 @@ __global__ __launch_bounds__(256) void hmat_z_kernel(const LrBlock *__restrict__
 // serial loop per leaf, a workgroup of 128 threads each: 256 workgroups on the
 // 10 242-vertex sphere, 2.51 ms a launch, 2.69 ms a product.  Cut into ranges,
 // with a column per group of 2m threads and eight loads in flight, the chip is
-// full: 0.39 ms a product (1.2 GB, 3.1 TB/s).
+// full: 0.39 ms a product (1.2 GB, 3.0 TB/s).
 struct RowSeg {
     int64_t off, src;
     int stride, half, cnt, kind;
