@@ -295,7 +295,7 @@ struct bem_mesh {
     std::map<bem::NearKey, std::unique_ptr<bem::DenseOperator>> dense_rounded_cache;   // of dense64
     std::map<bem::NearKey, std::unique_ptr<bem::HMatrix, bem::HMatDeleter>> hmat_cache;
     std::shared_ptr<bem::DenseShare> dense_share;   // set for serving replicas
-    bem::DevBuf<float2> xs32;          // scratch of the assembled products
+    bem::DevBuf<float2> xs32, xs64;    // scratch of the complex64 and complex128 products
 
     // OSRC: P1 vertex graph, M and S values, factor state per parameter set
     std::unique_ptr<bem::OsrcSymbolicState, bem::OsrcSymDeleter> osrc_sym;
@@ -454,7 +454,8 @@ const DenseOperator &dense_get(bem_mesh *m, double2 k0, double2 k1, double rho, 
 // right-hand sides, scratch in xs
 void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DevBuf<float2> &xs,
                 hipStream_t s);
-// scratch of the product of R >= 2 right-hand sides below the MFMA GEMM's count
+// scratch of the products of up to R right-hand sides on the matrix units; complex128:
+// of any number from 2 on, so that it never grows under a captured product
 int64_t dense_mx_scratch_bytes(int64_t N, int R, bool fp64);
 // Y = B X for R right-hand sides (x, y RHS-major [R][2N]) on MFMA
 void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hipStream_t s);

@@ -952,8 +952,6 @@ namespace {
 
 constexpr int MX_MAX_RHS = 32;   // right-hand sides per launch of the skinny product
 
-int mx_tiles(int nr) { return nr <= 8 ? 1 : nr <= 16 ? 2 : 4; }
-
 constexpr int MX_RT = 2;        // 16-row tiles per wavefront
 constexpr int MX_SPLITS = 32;   // ranges of K at most
 
@@ -993,12 +991,25 @@ template <class R, int NT> int64_t mx_range(int64_t M, int64_t Kp) {
     return best;
 }
 
+// Scratch of a launch: prepared columns, then the partial sums of the ranges.
+template <class R, int NT> int64_t mx_scratch(int64_t n2, int64_t klen) {
+    const int64_t Kp = 2 * n2, nsplit = (Kp + klen - 1) / klen;
+    return 16 * NT * (Kp * (int64_t)sizeof(R) + nsplit * n2 * (int64_t)sizeof(double));
+}
+template <class R, int NT> int64_t mx_scratch(int64_t n2) {
+    return mx_scratch<R, NT>(n2, mx_range<R, NT>(n2, 2 * n2));
+}
+
+// nr <= 8 NT right-hand sides in one launch; scratch in xs
 template <class R, int NT>
-void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, char *scratch,
+void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, DevBuf<float2> &xs,
                hipStream_t s) {
     const int64_t M = n2, Kp = 2 * n2;
     const int64_t klen = mx_range<R, NT>(M, Kp);
     const int nsplit = (int)((Kp + klen - 1) / klen);
+    if ((int64_t)xs.bytes() < mx_scratch<R, NT>(n2, klen))
+        xs.alloc((size_t)dense_mx_scratch_bytes(n2 / 2, nr, sizeof(R) == 8) / sizeof(float2));
+    char *scratch = (char *)xs.p;
     R *XT = (R *)scratch;
     double *part = (double *)(scratch + 16 * NT * Kp * (int64_t)sizeof(R));
     hipLaunchKernelGGL(mx_prep_kernel<R>, dim3(8 * NT, (unsigned)((n2 + 255) / 256)), dim3(256), 0, s, x,
@@ -1016,17 +1027,13 @@ void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, cha
     BEM_LAUNCH_CHECK();
 }
 
-// nr <= MX_MAX_RHS right-hand sides in one launch; scratch in xs
+// nr <= MX_MAX_RHS right-hand sides
 template <class T>
 void mx_apply(const T *B, int64_t n2, const double2 *x, double2 *y, int nr, DevBuf<float2> &xs,
               hipStream_t s) {
-    const size_t need = (size_t)dense_mx_scratch_bytes(n2 / 2, nr, sizeof(T) == 8) / sizeof(float2);
-    if (xs.n < need) xs.alloc(need);
-    switch (mx_tiles(nr)) {
-    case 1: mx_launch<T, 1>(B, n2, x, y, nr, (char *)xs.p, s); break;
-    case 2: mx_launch<T, 2>(B, n2, x, y, nr, (char *)xs.p, s); break;
-    default: mx_launch<T, 4>(B, n2, x, y, nr, (char *)xs.p, s); break;
-    }
+    if (nr <= 8) mx_launch<T, 1>(B, n2, x, y, nr, xs, s);
+    else if (nr <= 16) mx_launch<T, 2>(B, n2, x, y, nr, xs, s);
+    else mx_launch<T, 4>(B, n2, x, y, nr, xs, s);
 }
 
 // right-hand sides of the next launch when `left` remain: 24 to 32 share one (four
@@ -1037,8 +1044,15 @@ int mx_group(int left) { return left >= 24 ? std::min(left, MX_MAX_RHS) : std::m
 }   // namespace
 
 int64_t dense_mx_scratch_bytes(int64_t N, int R, bool fp64) {
-    const int64_t cols = 16 * mx_tiles(std::min(R, MX_MAX_RHS)), n2 = 2 * N;
-    return cols * 2 * n2 * (fp64 ? 8 : 4) + MX_SPLITS * n2 * cols * 8;
+    const int64_t n2 = 2 * N;
+    if (R < 2) return 0;
+    if (fp64)
+        return std::max(mx_scratch<double, 1>(n2),
+                        std::max(mx_scratch<double, 2>(n2), mx_scratch<double, 4>(n2)));
+    int64_t b = mx_scratch<float, 1>(n2);
+    if (R > 8) b = std::max(b, mx_scratch<float, 2>(n2));
+    if (R >= 24) b = std::max(b, mx_scratch<float, 4>(n2));
+    return b;
 }
 
 namespace {

@@ -98,7 +98,7 @@ struct Op {
         } else if (precision == BEM_FP32_HMAT) {
             for (int r = 0; r < R; r++) hmat_apply(*hm, m, *nf, in + r * 2 * m->N, out + r * 2 * m->N, s);
         } else if (precision == BEM_FP64 && dense64) {
-            dense_apply(*dense64, in, out, R, m->xs32, s);
+            dense_apply(*dense64, in, out, R, m->xs64, s);
         } else {
             farfield_apply_batch(m, *nf, k0, k1, rho, in, out, R, precision, s);
         }
@@ -124,7 +124,7 @@ struct Op {
             if (precision == BEM_FP32_DENSE || (precision == BEM_FP64 && dense64)) {
                 const bool f64 = precision == BEM_FP64;
                 dense_apply(dense_get(pm, k0, ko, ro, s, 1, nullptr, f64), px.p, py.p, R,
-                            pm->xs32, s);
+                            f64 ? pm->xs64 : pm->xs32, s);
             } else {
                 const NearOperator &nfo = nearfield_get(pm, k0, ko, ro, s);
                 farfield_apply_batch(pm, nfo, k0, ko, ro, px.p, py.p, R, precision, s);
@@ -463,7 +463,8 @@ int64_t solve_footprint(bem_mesh *m, double2 k0, double2 k1, double rho,
     if (o.path == 3) b += hmat_bytes_estimate(m, k0, k1, rho);
     if (dense) b += 2 * G * n2 * 8 + dense_gemm_scratch_bytes(m, G);
     if (o.path == 1)   // scratch of the assembled products
-        b += std::max(dense_mx_scratch_bytes(m->N, G, true), dense_mx_scratch_bytes(m->N, G, false));
+        b += (!dense || rdense ? dense_mx_scratch_bytes(m->N, G, true) : 0) +
+             (dense ? dense_mx_scratch_bytes(m->N, G, false) : 0);
     b += ((int64_t)n_waves + 8 * (int64_t)G) * n2 * c16;      // f, B, X, R, D, T, yw, vin, vout
     if (o.formulation == BEM_FORM_CALDERON) {
         b += 2 * (int64_t)G * n2 * c16;                       // t1, t2
