@@ -108,6 +108,7 @@ void mesh_trim(bem_mesh *m) {
     m->dyn64.release();
     m->dyn32.release();
     m->partial.release();
+    m->batch_part.release();
     m->trirows.release();
     m->sym32.release();
     m->sym64.release();
@@ -121,7 +122,7 @@ int64_t bem_mesh::device_bytes() const {
     int64_t b = geo64.bytes() + geo32.bytes() + tst.bytes() + tobj_d.bytes() + tri_d.bytes() +
                 star_ptr.bytes() + star_idx.bytes() + near_pairs.bytes() + nf_rowptr.bytes() +
                 nf_col.bytes() + nf_cptr.bytes() + nf_contrib.bytes() + ss_tab.bytes() +
-                dyn64.bytes() + dyn32.bytes() + partial.bytes() + trirows.bytes() +
+                dyn64.bytes() + dyn32.bytes() + partial.bytes() + batch_part.bytes() + trirows.bytes() +
                 sym32.items.bytes() + sym64.items.bytes() + field_work->bytes();
     for (const auto &kv : near_cache) b += kv.second->vals.bytes();
     for (const auto &kv : dense_cache) b += kv.second->bytes();

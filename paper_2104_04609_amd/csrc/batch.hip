@@ -725,8 +725,8 @@ void batch_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const double2 
     int nsplit = 1, len = T;
     batch_plan<R, C>(m, code, &nsplit, &len);
     const size_t np = (size_t)nsplit * T * 6 * cols, nx = (size_t)N * 2 * cols;
-    if (m->partial.n < np + nx) m->partial.alloc(np + nx);
-    double *part = m->partial.p, *xt = part + np;
+    if (m->batch_part.n < np + nx) m->batch_part.alloc(np + nx);
+    double *part = m->batch_part.p, *xt = part + np;
     auto &itab = [&]() -> auto & {
         if constexpr (F32) return nf.dtab32;
         else return nf.dtab64;

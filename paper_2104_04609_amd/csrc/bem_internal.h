@@ -304,7 +304,8 @@ struct bem_mesh {
     // scratch (grown on demand)
     bem::DevBuf<double> dyn64;
     bem::DevBuf<float> dyn32;
-    bem::DevBuf<double> partial;
+    bem::DevBuf<double> partial;         // of single-vector products, either precision
+    bem::DevBuf<double> batch_part;      // of products that share launches
     bem::DevBuf<double> trirows;
     // work items of the symmetric pair kernel, and the plan that they are of: one set
     // per precision, so that products of the two in turn leave each other's in place

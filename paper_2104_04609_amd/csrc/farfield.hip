@@ -1554,6 +1554,9 @@ template <class R> const SymPlan &sym_plan_for(const bem_mesh *m, const FarPlan 
     return sym_plan((int)m->T, fp.blk, far_slots((const void *)sym_kernel<R>(fp.code, fp.fr), fp.blk,
                                                  sym_smem<R>(fp.blk)));
 }
+size_t sym_partials(const SymPlan &p) {
+    return (size_t)(p.tau_doubles + p.sig_doubles + p.acc_doubles);
+}
 
 
 }   // namespace
@@ -1575,7 +1578,7 @@ int64_t farfield_scratch_bytes(const bem_mesh *m, int precision, double2 k0, dou
                                       (int64_t)sp.items.size() * 4);
         }
     }
-    if (R >= farfield_batch_min) part = std::max(part, farfield_mx_bytes(m, precision, k0, k1, R));
+    if (R >= farfield_batch_min) part += farfield_mx_bytes(m, precision, k0, k1, R);
     return dyn + part + T * ROW_STRIDE * 8;
 }
 
@@ -1607,8 +1610,16 @@ void far_apply(bem_mesh *m, const NearOperator &nf, double2 k0, const FarPlan &p
     if (tuning().farfield_symmetric) {
         // each separated pair once, rows of both triangles
         const SymPlan &sp = sym_plan_for<R>(m, plan);
-        const size_t sneed = (size_t)(sp.tau_doubles + sp.sig_doubles + sp.acc_doubles);
-        if (m->partial.n < sneed) m->partial.alloc(sneed);
+        if (m->partial.n < sym_partials(sp)) {
+            // room for either precision: a captured product of one keeps its buffer
+            // when the other is used
+            const SymPlan &other = [&]() -> const SymPlan & {
+                if constexpr (F32)
+                    return sym_plan_for<double>(m, far_plan(m, BEM_FP64, k0, nf.k1_plan, blk));
+                else return sym_plan_for<float>(m, far_plan(m, BEM_FP32, k0, nf.k1_plan, blk));
+            }();
+            m->partial.alloc(std::max(sym_partials(sp), sym_partials(other)));
+        }
         bem_mesh::SymItems &si = F32 ? m->sym32 : m->sym64;
         if (si.items.n < sp.items.size() || si.plan != &sp) {
             if (si.items.n < sp.items.size()) si.items.alloc(sp.items.size());
