@@ -103,8 +103,7 @@ void mesh_trim(bem_mesh *m) {
     m->dense_rounded_cache.clear();
     m->hmat_cache.clear();
     m->osrc_cache.clear();
-    m->xs32.release();
-    m->xs64.release();
+    m->dense_scratch.release();
     m->dyn64.release();
     m->dyn32.release();
     m->partial.release();
@@ -129,7 +128,7 @@ int64_t bem_mesh::device_bytes() const {
     for (const auto &kv : dense64_cache) b += kv.second->bytes();
     for (const auto &kv : dense_rounded_cache) b += kv.second->bytes();
     for (const auto &kv : hmat_cache) b += bem::hmat_bytes(*kv.second);
-    b += xs32.bytes() + xs64.bytes();
+    b += dense_scratch.bytes();
     for (const auto &kv : osrc_cache) b += bem::osrc_bytes(*kv.second);
     if (osrc_sym) b += bem::osrc_sym_bytes(*osrc_sym);
     for (const auto &pm : parts) b += pm->device_bytes();
@@ -239,7 +238,7 @@ void operator_matvec(const bem_mesh *mesh, bem_c64 k_ext, bem_c64 k_int, double 
     if (precision == BEM_FP32_DENSE || precision == BEM_FP64_DENSE) {
         const bem::DenseOperator &op =
             bem::dense_get(m, k0, k1, rho, s, s1, om, precision == BEM_FP64_DENSE);
-        bem::dense_apply(op, (const double2 *)x, (double2 *)y, n_rhs, op.fp64 ? m->xs64 : m->xs32, s);
+        bem::dense_apply(op, (const double2 *)x, (double2 *)y, n_rhs, m->dense_scratch, s);
         return;
     }
     if (precision == BEM_FP32_HMAT) {

@@ -143,6 +143,23 @@ struct NearOperator {
     mutable DevBuf<double> dtab64;
 };
 
+// Scratch of the assembled products.  Complex64: one buffer, grown on demand.
+// Complex128: one for launches of up to 8, 16 and 32 vectors each, made at first use
+// and never replaced, so that a captured product keeps its own.
+struct DenseScratch {
+    DevBuf<float2> xs;
+    DevBuf<float2> wide[3];
+    void release() {
+        xs.release();
+        for (auto &b : wide) b.release();
+    }
+    int64_t bytes() const {
+        int64_t n = xs.bytes();
+        for (const auto &b : wide) n += b.bytes();
+        return n;
+    }
+};
+
 // Interior materials of the objects when they differ (Sec. 2.7, several
 // scatterers): k_m and rho_m = rho_int,m / rho_ext per object.
 struct ObjMaterials {
@@ -295,7 +312,7 @@ struct bem_mesh {
     std::map<bem::NearKey, std::unique_ptr<bem::DenseOperator>> dense_rounded_cache;   // of dense64
     std::map<bem::NearKey, std::unique_ptr<bem::HMatrix, bem::HMatDeleter>> hmat_cache;
     std::shared_ptr<bem::DenseShare> dense_share;   // set for serving replicas
-    bem::DevBuf<float2> xs32, xs64;    // scratch of the complex64 and complex128 products
+    bem::DenseScratch dense_scratch;   // of the assembled products
 
     // OSRC: P1 vertex graph, M and S values, factor state per parameter set
     std::unique_ptr<bem::OsrcSymbolicState, bem::OsrcSymDeleter> osrc_sym;
@@ -452,18 +469,17 @@ std::unique_ptr<DenseOperator> dense_assemble(bem_mesh *m, const NearOperator &n
 const DenseOperator &dense_get(bem_mesh *m, double2 k0, double2 k1, double rho, hipStream_t s,
                                int s1 = 1, const ObjMaterials *om = nullptr, bool fp64 = false);
 // y_r = B x_r, r < R (x, y RHS-major [R][2N]): product reading B once per 32
-// right-hand sides, scratch in xs
-void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DevBuf<float2> &xs,
+// right-hand sides
+void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DenseScratch &sc,
                 hipStream_t s);
-// scratch of the products of up to R right-hand sides on the matrix units; complex128:
-// of any number from 2 on, so that it never grows under a captured product
+// scratch of the products of up to R right-hand sides on the matrix units
 int64_t dense_mx_scratch_bytes(int64_t N, int R, bool fp64);
 // Y = B X for R right-hand sides (x, y RHS-major [R][2N]) on MFMA
 void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hipStream_t s);
 int64_t dense_gemm_scratch_bytes(const bem_mesh *m, int R);
 // MFMA product from tuning().dense_gemm_min_rhs right-hand sides, else dense_gemv
 void dense_apply(const DenseOperator &op, const double2 *x, double2 *y, int R,
-                 DevBuf<float2> &xs, hipStream_t s, const TuneEntry *forced = nullptr);
+                 DenseScratch &sc, hipStream_t s, const TuneEntry *forced = nullptr);
 
 // Issue rates (lane operations per second over the device) of v_fma_f32,
 // v_sin_f32, v_cos_f32, v_rsq_f32 and v_fma_f64; rates[5].

@@ -1000,16 +1000,17 @@ template <class R, int NT> int64_t mx_scratch(int64_t n2) {
     return mx_scratch<R, NT>(n2, mx_range<R, NT>(n2, 2 * n2));
 }
 
-// nr <= 8 NT right-hand sides in one launch; scratch in xs
+// nr <= 8 NT right-hand sides in one launch
 template <class R, int NT>
-void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, DevBuf<float2> &xs,
+void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, DenseScratch &sc,
                hipStream_t s) {
     const int64_t M = n2, Kp = 2 * n2;
     const int64_t klen = mx_range<R, NT>(M, Kp);
     const int nsplit = (int)((Kp + klen - 1) / klen);
-    if ((int64_t)xs.bytes() < mx_scratch<R, NT>(n2, klen))
-        xs.alloc((size_t)dense_mx_scratch_bytes(n2 / 2, nr, sizeof(R) == 8) / sizeof(float2));
-    char *scratch = (char *)xs.p;
+    DevBuf<float2> &buf = std::is_same<R, double>::value ? sc.wide[NT / 2] : sc.xs;
+    const size_t need = (size_t)mx_scratch<R, NT>(n2, klen) / sizeof(float2);
+    if (buf.n < need) buf.alloc(need);
+    char *scratch = (char *)buf.p;
     R *XT = (R *)scratch;
     double *part = (double *)(scratch + 16 * NT * Kp * (int64_t)sizeof(R));
     hipLaunchKernelGGL(mx_prep_kernel<R>, dim3(8 * NT, (unsigned)((n2 + 255) / 256)), dim3(256), 0, s, x,
@@ -1029,11 +1030,11 @@ void mx_launch(const R *B, int64_t n2, const double2 *x, double2 *y, int nr, Dev
 
 // nr <= MX_MAX_RHS right-hand sides
 template <class T>
-void mx_apply(const T *B, int64_t n2, const double2 *x, double2 *y, int nr, DevBuf<float2> &xs,
+void mx_apply(const T *B, int64_t n2, const double2 *x, double2 *y, int nr, DenseScratch &sc,
               hipStream_t s) {
-    if (nr <= 8) mx_launch<T, 1>(B, n2, x, y, nr, xs, s);
-    else if (nr <= 16) mx_launch<T, 2>(B, n2, x, y, nr, xs, s);
-    else mx_launch<T, 4>(B, n2, x, y, nr, xs, s);
+    if (nr <= 8) mx_launch<T, 1>(B, n2, x, y, nr, sc, s);
+    else if (nr <= 16) mx_launch<T, 2>(B, n2, x, y, nr, sc, s);
+    else mx_launch<T, 4>(B, n2, x, y, nr, sc, s);
 }
 
 // right-hand sides of the next launch when `left` remain: 24 to 32 share one (four
@@ -1047,8 +1048,8 @@ int64_t dense_mx_scratch_bytes(int64_t N, int R, bool fp64) {
     const int64_t n2 = 2 * N;
     if (R < 2) return 0;
     if (fp64)
-        return std::max(mx_scratch<double, 1>(n2),
-                        std::max(mx_scratch<double, 2>(n2), mx_scratch<double, 4>(n2)));
+        return mx_scratch<double, 1>(n2) + (R > 8 ? mx_scratch<double, 2>(n2) : 0) +
+               (R >= 24 ? mx_scratch<double, 4>(n2) : 0);
     int64_t b = mx_scratch<float, 1>(n2);
     if (R > 8) b = std::max(b, mx_scratch<float, 2>(n2));
     if (R >= 24) b = std::max(b, mx_scratch<float, 4>(n2));
@@ -1090,7 +1091,7 @@ constexpr int GEMV_RHS = 8;   // vectors of a launch on the vector units at most
 
 }   // namespace
 
-void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DevBuf<float2> &xs,
+void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, DenseScratch &sc,
                 hipStream_t s) {
     const int64_t n2 = op.n2;
     for (int r0 = 0; r0 < R;) {
@@ -1099,10 +1100,11 @@ void dense_gemv(const DenseOperator &op, const double2 *x, double2 *y, int R, De
         int nr = R - r0;
         if (nr > gemv_max_rhs(n2)) {
             nr = mx_group(nr);
-            mx_apply((const float *)op.B.p, n2, xr, yr, nr, xs, s);
+            mx_apply((const float *)op.B.p, n2, xr, yr, nr, sc, s);
         } else {
             nr = std::min(nr, GEMV_RHS);
             const int64_t cnt = nr * n2;
+            DevBuf<float2> &xs = sc.xs;
             if (xs.n < (size_t)cnt) xs.alloc((size_t)cnt);
             hipLaunchKernelGGL(to_c64_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, xr,
                                xs.p, cnt);
@@ -1171,7 +1173,7 @@ int gemm_kchunk(int64_t mtiles, int64_t Kp) {
 }   // namespace
 
 void dense_apply(const DenseOperator &op, const double2 *x, double2 *y, int R,
-                 DevBuf<float2> &xs, hipStream_t s, const TuneEntry *forced) {
+                 DenseScratch &sc, hipStream_t s, const TuneEntry *forced) {
     if (op.fp64) {
         for (int r0 = 0; r0 < R;) {
             int nr = mx_group(R - r0);
@@ -1179,7 +1181,7 @@ void dense_apply(const DenseOperator &op, const double2 *x, double2 *y, int R,
             const double2 *xr = x + r0 * op.n2;
             double2 *yr = y + r0 * op.n2;
             if (nr > 1) {
-                mx_apply((const double *)op.B64.p, op.n2, xr, yr, nr, xs, s);
+                mx_apply((const double *)op.B64.p, op.n2, xr, yr, nr, sc, s);
             } else {
                 Timer tm("dense_gemv_fp64", s);
                 hipLaunchKernelGGL(dense_gemv64_kernel,
@@ -1193,7 +1195,7 @@ void dense_apply(const DenseOperator &op, const double2 *x, double2 *y, int R,
     }
     const TuneEntry te = forced ? *forced : tune_lookup(op.T, R);
     if (R >= te.gemm_min) dense_gemm(op, x, y, R, s);
-    else dense_gemv(op, x, y, R, xs, s);
+    else dense_gemv(op, x, y, R, sc, s);
 }
 
 void dense_gemm(const DenseOperator &op, const double2 *x, double2 *y, int R, hipStream_t s) {

@@ -94,11 +94,11 @@ struct Op {
     DevBuf<double2> px, py;                  // one object's entries [R][2 N_m]
     void weak(const double2 *in, double2 *out, int R, int precision) {
         if (precision == BEM_FP32_DENSE) {
-            dense_apply(*dense, in, out, R, m->xs32, s);
+            dense_apply(*dense, in, out, R, m->dense_scratch, s);
         } else if (precision == BEM_FP32_HMAT) {
             for (int r = 0; r < R; r++) hmat_apply(*hm, m, *nf, in + r * 2 * m->N, out + r * 2 * m->N, s);
         } else if (precision == BEM_FP64 && dense64) {
-            dense_apply(*dense64, in, out, R, m->xs64, s);
+            dense_apply(*dense64, in, out, R, m->dense_scratch, s);
         } else {
             farfield_apply_batch(m, *nf, k0, k1, rho, in, out, R, precision, s);
         }
@@ -124,7 +124,7 @@ struct Op {
             if (precision == BEM_FP32_DENSE || (precision == BEM_FP64 && dense64)) {
                 const bool f64 = precision == BEM_FP64;
                 dense_apply(dense_get(pm, k0, ko, ro, s, 1, nullptr, f64), px.p, py.p, R,
-                            f64 ? pm->xs64 : pm->xs32, s);
+                            pm->dense_scratch, s);
             } else {
                 const NearOperator &nfo = nearfield_get(pm, k0, ko, ro, s);
                 farfield_apply_batch(pm, nfo, k0, ko, ro, px.p, py.p, R, precision, s);

@@ -206,7 +206,7 @@ TuneEntry autotune(bem_mesh *m, double2 k0, double2 k1, double rho, int R, int e
         std::unique_ptr<DenseOperator> op = dense_assemble(m, nf, k0, k1, rho, s);
         BEM_HIP(hipStreamSynchronize(s));
         best.t_asm = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-        DevBuf<float2> xs;
+        DenseScratch xs;
         TuneEntry c = best;
         c.gemm_min = R + 1;   // up to 32 vectors per pass
         const double t_small = time_best([&] { dense_apply(*op, X.p, Y.p, R, xs, s, &c); }, s);
